@@ -33,7 +33,8 @@ namespace nmc {
 //    level l's N cells per axis by the inverse passes (out: level l's
 //    potential, to which the reduced values and the carry S are added);
 //  * kind 4 (modified method), kind 2's grid with full output: out gets the
-//    hole potential on all N^3 cells and Sout its stencil box;
+//    hole potential on all N^3 cells and Sout its stencil box (plane passes,
+//    original method without restriction: out null, the box alone);
 //  * kind 5 (three-level scheme of Appendix B), kind 3 with the input's
 //    child region zeroed (the doubled hole grid).  Kinds 3 and 5 also serve
 //    at scale 4 (quadrupled grid: 4N cells of level l+2's spacing, period

@@ -689,6 +689,7 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
   std::vector<FieldDesc> quads;  // quadrupled grids
   const size_t lvl = (size_t)N * N * N;
   std::vector<FieldDesc> fulls, secs;  // full grids; hole grids or child-region boxes
+  std::vector<FieldDesc> zeroed;       // hole grids on the stencil box, plane by plane (kind 4)
   std::vector<int> full_level;
   struct RestrictStep {
     const R* fine;
@@ -812,19 +813,26 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
       } else if (finer) {
         FieldDesc c{};
         c.rho = f.rho;
-        const bool box = boxes || planes;
+        // A coarse density that the caller keeps under the finer grid may be
+        // anything (1e8 times the rest, not a number): Phi^l - C would leave its
+        // rounding on every finer level.  Below N = 128, whose layout has room
+        // for it, the level with its child region zeroed is convolved instead
+        // (kind 4, the stencil box its only output).
+        const bool hole = planes && !restrict_on && !lo.boxes;
+        const bool box = (boxes || planes) && !hole;
         c.rc = box ? f.rc : nullptr;
         c.rslab = f.rslab;
         c.rdepth = f.rdepth;
         c.A = base + lo.As(l);
-        c.B = planes || box_planes ? base + lo.As(l) + behind(PB, N / 2) : base + lo.Bs(l);
-        c.C = planes ? f.B : nullptr;  // the level's planes, for Phi^l - C
-        c.out = base + lo.Box(l);
+        c.B = planes || box_planes ? base + lo.As(l) + behind(hole ? PL : PB, hole ? N : N / 2) : base + lo.Bs(l);
+        c.C = planes && box ? f.B : nullptr;  // the level's planes, for Phi^l - C
+        c.out = hole ? nullptr : base + lo.Box(l);
+        c.Sout = hole ? base + lo.Box(l) : nullptr;
         c.scale = box ? 8 * f.scale : f.scale;  // -G h^2 over the cube of the grid's own period
-        c.kind = box ? 1 : 2;
+        c.kind = box ? 1 : hole ? 4 : 2;
         c.comp = f.comp;
         c.tri = f.tri;
-        secs.push_back(c);
+        (hole ? zeroed : secs).push_back(c);
       }
     }
   }
@@ -994,14 +1002,17 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
   const bool one_stream = (reqs[0].flags & NMC_ONE_STREAM) != 0;
   const bool fused = nmc::plane_passes_fit<R>(P) && !separate;
   if (planes && !mod) {
-    // every grid shares the X and YZ launches; the hole potentials Phi^l - C
-    // on the stencil boxes, the carry cascade, then the levels
+    // every grid shares the X and YZ launches; the hole potentials (Phi^l - C,
+    // or a hole grid's own) on the stencil boxes, the carry cascade, then the
+    // levels
     if ((rc = restrict_cascade(s))) return rc;
     std::vector<FieldDesc> all(fulls);
+    all.insert(all.end(), zeroed.begin(), zeroed.end());
     all.insert(all.end(), secs.begin(), secs.end());
     NMC_HIP(ctx, for_planes(all, plan, true, nmc::launch_plane_x<R>, NMC_PASS_X, s));
     NMC_HIP(ctx, for_planes(all, plan, true, nmc::launch_plane_yz<R>, NMC_PASS_Z, s));
     NMC_HIP(ctx, for_planes(secs, plan, true, nmc::launch_plane_ix_box<R>, NMC_PASS_IX_SECOND, s));
+    NMC_HIP(ctx, for_planes(zeroed, plan, true, nmc::launch_plane_ix<R>, NMC_PASS_IX_SECOND, s));
     if ((rc = carry_cascade(s))) return rc;
     NMC_HIP(ctx, for_planes(fulls, plan, true, nmc::launch_plane_ix<R>, NMC_PASS_IX_FULL, s));
     return NMC_OK;

@@ -1,0 +1,52 @@
+"""NMC_NO_RESTRICT: a coarse density kept under a finer grid reaches the coarse
+level's own potential only.  Whatever it holds there (1e8 times the rest, not a
+number), the finer levels see the hole potential (Sect. 4, Fig. 5) to the
+accuracy of any other solve, at every size whose levels are convolved plane by
+plane with room for a hole grid."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2301_06763_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = {torch.float64: 1e-12, torch.float32: 1e-5}  # the pointwise bounds of every parity test
+
+
+@pytest.mark.timeout(120)
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("N", [36, 64, 96, 100, 124])
+@pytest.mark.parametrize("trilinear", [False, True])
+def test_finer_levels_do_not_see_it(dtype, N, trilinear):
+    from paper_2301_06763_amd import nmc
+    if trilinear and N > 64:
+        pytest.skip("the carry rule is independent of N")
+    L = 3
+    w = inputs.random_levels(N, L, seed=60 + N)
+    c = slice(N // 4, 3 * N // 4)
+    zeroed = w.rho.clone()
+    zeroed[:-1, c, c, c] = 0
+    flags = nmc.NMC_NO_RESTRICT | (nmc.NMC_PROLONG_TRILINEAR if trilinear else 0)
+    ref = oracle.solve(zeroed.numpy(), w.h0, restrict=False, trilinear=trilinear)
+    other = w.rho.to("cuda", dtype)
+    ctx = nmc.Context()
+    try:
+        for junk in (1e8, float("nan")):
+            rho = other.clone()
+            rho[0, c, c, c] *= junk
+            rho[1, c, c, c] = 0
+            print(f"kept coarse N={N} {dtype} {junk}", flush=True)
+            got = ctx.solve(rho, w.h0, 1.0, flags)
+            torch.cuda.synchronize()
+            r = got[1:].double().cpu().numpy()
+            assert np.max(np.abs(r - ref[1:]) / np.abs(ref[1:])) < TOL[dtype]
+            # one launch sequence with meshes that restrict: bitwise the same
+            alone = ctx.solve(other, w.h0, 1.0, flags & ~nmc.NMC_NO_RESTRICT)
+            reqs = [(other, w.h0, 1.0, flags & ~nmc.NMC_NO_RESTRICT), (rho, w.h0, 1.0, flags)]
+            both = ctx.solve_batch(reqs)
+            torch.cuda.synchronize()
+            assert torch.equal(both[0], alone) and torch.equal(both[1][1:], got[1:])
+    finally:
+        ctx.close()
