@@ -205,9 +205,34 @@ struct PlaneTables {
   const T* twb;  // the same of the boxes' period
   const R* gpb;
 };
-int plane_classes(int P);  // C of a period of the plane passes
-template <class R> bool plane_plan(int N, PlanePlan*);      // plan of a level of N cells, if it has one
-template <class R> bool plane_box_plan(int P, PlanePlan*);  // plan of boxes of period P
+// Period of a level of N cells: the smallest of 2 NP and 3 NP, NP a power of
+// two from 32, that holds 2N - 1 points, where its planes fit a workgroup: up
+// to NP = 128 in FP32 and 64 in FP64 (160 KB of LDS).  Levels of up to 32
+// cells take the fused plane passes of kernels.hip: there every launch is a
+// few microseconds of latency, and the YZ pass chains four transforms per
+// class (32^3 x 3 FP64: 37.7 us a solve here, 31.6 there).
+template <class R>
+bool plane_plan(int N, PlanePlan* out) {
+  if (N <= 32) return false;
+  for (int NP = 32; NP <= (sizeof(R) == 4 ? 128 : 64); NP *= 2)
+    for (int C = 2; C <= 3; ++C)
+      if (C * NP >= 2 * N && (NP < 128 || C == 2)) {
+        *out = PlanePlan{NP, C};
+        return true;
+      }
+  return false;
+}
+
+// C of a period of the plane passes.
+inline int plane_classes(int P) { return P % 5 == 0 ? 5 : P % 3 == 0 ? 3 : 2; }
+
+// Whether child-region boxes of period P run plane by plane.
+template <class R>
+bool plane_box_plan(int P, PlanePlan* out) {
+  const int C = plane_classes(P);
+  *out = PlanePlan{P / C, C};
+  return out->NP >= 4 && out->NP <= (sizeof(R) == 4 ? 128 : 64) && (out->NP < 128 || C == 2);
+}
 template <class R> hipError_t launch_plane_x(const FieldTable&, PlaneGeom, PlaneTables<R>, hipStream_t);
 template <class R> hipError_t launch_plane_yz(const FieldTable&, PlaneGeom, PlaneTables<R>, hipStream_t);
 // Levels: the potential, with the carry S when set.
@@ -215,11 +240,24 @@ template <class R> hipError_t launch_plane_ix(const FieldTable&, PlaneGeom, Plan
 // Boxes: C on the stencil box; joint: the hole potential Phi^l - C there, the
 // level's O in FieldDesc::C.
 template <class R> hipError_t launch_plane_ix_box(const FieldTable&, PlaneGeom, PlaneTables<R>, hipStream_t);
+// Points per class of the scaled grids of levels of N cells: the power of two
+// from N, where a plane fits a workgroup (as plane_plan); 0 if none does.  Faster
+// than the passes at 4N and 8N at every such N (three levels, FP64: N = 8 48 ->
+// 37 us, 20 70 -> 56, 64 146 -> 104; three-level method 99 -> 81, 117 -> 94,
+// 526 -> 199).  N = 4
+// stays with the passes of kernels.hip (its parts would not fit the workspace
+// of a level on 8 points).
+template <class R>
+int scaled_points(int N) {
+  if (N < 8) return 0;
+  int NP = 8;
+  while (NP < N) NP *= 2;
+  return NP <= (sizeof(R) == 4 ? 128 : 64) ? NP : 0;
+}
 // Scaled grids (kinds 3 and 5, scale S = 2 or 4) plane by plane
 // (plane_scaled.hip), all of one launch of nfull grids; tw and gp of PlaneTables
 // are those of their period (S + 1) scaled_points.  The IX pass adds the means
 // (and the carry S when set) to out.
-template <class R> int scaled_points(int N);  // points per class, 0: not plane by plane
 template <class R> hipError_t launch_scaled_x(const FieldTable&, PlaneGeom, int S, PlaneTables<R>, hipStream_t);
 template <class R> hipError_t launch_scaled_yz(const FieldTable&, PlaneGeom, int S, PlaneTables<R>, hipStream_t);
 template <class R> hipError_t launch_scaled_ix(const FieldTable&, PlaneGeom, int S, PlaneTables<R>, hipStream_t);

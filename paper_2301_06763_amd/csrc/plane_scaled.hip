@@ -377,21 +377,6 @@ __global__ void __launch_bounds__((S + 1) * (x_threads<NP, S + 1>())) k_scaled_i
 }
 
 // ---------------------------------------------------------------------------
-// Points per class of the scaled grids of levels of N cells: the power of two
-// from N, where a plane fits a workgroup (as plane_plan); 0 if none does.  Faster
-// than the passes at 4N and 8N at every such N (three levels, FP64: N = 8 48 ->
-// 37 us, 20 70 -> 56, 64 146 -> 104; three-level method 99 -> 81, 117 -> 94,
-// 526 -> 199).  N = 4
-// stays with the passes of kernels.hip (its parts would not fit the workspace
-// of a level on 8 points).
-template <class R>
-int scaled_points(int N) {
-  if (N < 8) return 0;
-  int NP = 8;
-  while (NP < N) NP *= 2;
-  return NP <= (sizeof(R) == 4 ? 128 : 64) ? NP : 0;
-}
-
 template <class R, class F>
 static hipError_t dispatch_scaled(int N, int S, F&& f) {
   auto both = [&](auto np) {
@@ -443,7 +428,6 @@ hipError_t launch_scaled_ix(const FieldTable& ft, PlaneGeom g, int S, PlaneTable
 }
 
 #define NMC_INSTANTIATE(R)                                                                                \
-  template int scaled_points<R>(int);                                                                     \
   template hipError_t launch_scaled_x<R>(const FieldTable&, PlaneGeom, int, PlaneTables<R>, hipStream_t); \
   template hipError_t launch_scaled_yz<R>(const FieldTable&, PlaneGeom, int, PlaneTables<R>, hipStream_t); \
   template hipError_t launch_scaled_ix<R>(const FieldTable&, PlaneGeom, int, PlaneTables<R>, hipStream_t);
