@@ -1304,6 +1304,19 @@ int solve_many(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s, Lease* l
 
 // --- kept workspace -----------------------------------------------------------------
 
+// A kept block back to the pool once its last use has completed: its own event
+// says so, whatever queue the stream's handle names by now (the null stream's
+// is recorded here).
+int retire_kept(nmc_ctx* ctx, std::vector<Kept>::iterator k) {
+  Lease l;
+  l.blocks.push_back(k->ws);
+  l.ev = k->ev;
+  ctx->kept.erase(k);
+  if (!l.ev) return lease_close(ctx, std::move(l), nullptr, &ctx->leases);
+  ctx->leases.push_back(std::move(l));
+  return NMC_OK;
+}
+
 // Workspace of `bytes` for solves on stream s, ordered after the stream's
 // earlier ones; *out is valid until the next call that may allocate.
 int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_t s, Kept** out) {
@@ -1314,12 +1327,7 @@ int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_
   if (rc) return rc;
   auto it = of_stream();
   if (it != ctx->kept.end() && it->ws.bytes < bytes) {
-    // too small: back to the pool once the work enqueued so far has completed
-    Lease l;
-    l.blocks.push_back(it->ws);
-    if (it->ev) (void)hipEventDestroy(it->ev);
-    ctx->kept.erase(it);
-    if ((rc = lease_close(ctx, std::move(l), s, &ctx->leases))) return rc;
+    if ((rc = retire_kept(ctx, it))) return rc;  // too small
     it = ctx->kept.end();
   }
   if (it == ctx->kept.end()) {

@@ -1,0 +1,295 @@
+// The library's runtime (csrc/runtime.cpp, whole) on the CPU, against a model
+// of streams, events and device memory in place of HIP and of the kernels.
+//
+// Every kernel launch is an operation ordered after what its stream has
+// enqueued or waited for and after what the host has waited for.  Nothing
+// finishes by itself: an operation is complete only once the host has waited
+// for it, so a query answers "not ready" until then, and every wait of the
+// host for unfinished work is counted.  Two calls whose operations use one
+// workspace block without being ordered are a race; so is any use of a block
+// that a captured graph refers to.
+#include <cstdio>
+#include <cstdlib>
+#include <set>
+
+#define __HIP_PLATFORM_AMD__ 1
+#define __align__(n)
+#define HIP_SYMBOL(x) (&x)
+#include "../paper_2301_06763_amd/csrc/runtime.cpp"
+
+namespace {
+
+using Ops = std::set<int>;
+struct Stream {
+  Ops before;  // operations the next one is ordered after
+  bool capturing = false;
+};
+struct Event {
+  Ops marks;
+  bool captured = false;
+};
+struct Mem {
+  size_t bytes;
+  std::vector<std::pair<int, int>> uses;  // (operation, call)
+  bool in_graph = false;
+};
+std::map<hipStream_t, Stream> g_streams;
+std::map<hipEvent_t, Event> g_events;
+std::map<char*, Mem> g_mem;
+Ops g_done;            // what the host knows to be complete
+char* g_next = (char*)0x100000000;
+size_t g_held = 0, g_capacity = ~size_t(0);
+int g_ops = 0, g_call = 0, g_races = 0, g_waits = 0, g_streams_made = 0;
+int g_fail_at = -1;    // launch number (from now) that fails
+int g_mallocs = 0, g_launches = 0;
+
+void wait_for(const Ops& o) {
+  if (!std::includes(g_done.begin(), g_done.end(), o.begin(), o.end())) ++g_waits;
+  g_done.insert(o.begin(), o.end());
+}
+Ops all_ops() {
+  Ops o;
+  for (int i = 0; i < g_ops; ++i) o.insert(i);
+  return o;
+}
+Mem* block_of(const void* p) {
+  auto it = g_mem.upper_bound((char*)p);
+  if (it == g_mem.begin()) return nullptr;
+  --it;
+  return (char*)p < it->first + it->second.bytes ? &it->second : nullptr;
+}
+void use(const void* p, hipStream_t s, int op) {
+  Mem* m = block_of(p);
+  if (!m) {
+    if (p) return;  // the caller's, or the static scratch
+    ++g_races;
+    std::printf("null buffer\n");
+    return;
+  }
+  const Stream& st = g_streams[s];
+  for (auto [o, call] : m->uses)
+    if (call != g_call && !st.before.count(o) && !g_done.count(o)) {
+      ++g_races;
+      std::printf("race: operation %d of call %d and %d of call %d\n", o, call, op, g_call);
+      break;
+    }
+  if (m->in_graph && !(m->uses.size() && m->uses.back().second == g_call)) {
+    ++g_races;
+    std::printf("call %d uses a captured graph's block\n", g_call);
+  }
+  m->uses.push_back({op, g_call});
+  if (st.capturing) m->in_graph = true;
+}
+hipError_t op_on(hipStream_t s, std::initializer_list<const void*> bufs) {
+  ++g_launches;
+  if (g_fail_at >= 0 && g_fail_at-- == 0) return hipErrorLaunchFailure;
+  const int op = g_ops++;
+  for (const void* p : bufs) use(p, s, op);
+  g_streams[s].before.insert(op);
+  return hipSuccess;
+}
+hipError_t grids(const nmc::FieldTable& ft, int n, hipStream_t s) {
+  ++g_launches;
+  if (g_fail_at >= 0 && g_fail_at-- == 0) return hipErrorLaunchFailure;
+  const int op = g_ops++;
+  for (int i = 0; i < n; ++i) use(ft.f[i].A, s, op), use(ft.f[i].B, s, op);
+  g_streams[s].before.insert(op);
+  return hipSuccess;
+}
+int g_no_table = 0;
+void table(const void* p, size_t bytes) {  // a Green table of this size
+  Mem* m = block_of(p);
+  if (!m || m->bytes < bytes) ++g_no_table, std::printf("table missing or of another size (%zu)\n", bytes);
+}
+size_t cube(int P, size_t r) { return (size_t)(P / 2 + 1) * (P / 2 + 1) * (P / 2 + 1) * r; }
+
+}  // namespace
+
+// --- HIP ----------------------------------------------------------------------
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  ++g_mallocs;
+  if (g_held + n > g_capacity) return hipErrorOutOfMemory;
+  g_held += n;
+  *p = g_next;
+  g_mem[g_next] = Mem{n, {}, false};
+  g_next += (n + 4095) / 4096 * 4096 + 4096;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  if (!p) return hipSuccess;
+  wait_for(all_ops());
+  auto it = g_mem.find((char*)p);
+  if (it == g_mem.end()) std::printf("free of an unknown block\n"), std::abort();
+  if (it->second.in_graph) ++g_races, std::printf("a captured graph's block freed\n");
+  g_held -= it->second.bytes;
+  g_mem.erase(it);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = (hipStream_t)(uintptr_t)(0x1000 + 16 * ++g_streams_made);
+  g_streams[*s] = Stream{};
+  return hipSuccess;
+}
+hipError_t hipStreamDestroy(hipStream_t s) { return g_streams.erase(s), hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { return wait_for(g_streams[s].before), hipSuccess; }
+hipError_t hipDeviceSynchronize() { return wait_for(all_ops()), hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  const Ops& m = g_events[e].marks;
+  g_streams[s].before.insert(m.begin(), m.end());
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  *st = g_streams[s].capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  static uintptr_t n = 0x900000;
+  *e = (hipEvent_t)(n += 16);
+  g_events[*e] = Event{};
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventDestroy(hipEvent_t e) {
+  if (!g_events.erase(e)) std::printf("event destroyed twice\n"), std::abort();
+  return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  g_events[e] = Event{g_streams[s].before, g_streams[s].capturing};
+  return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) {
+  const Event& v = g_events[e];
+  if (v.captured) return hipErrorCapturedEvent;
+  return std::includes(g_done.begin(), g_done.end(), v.marks.begin(), v.marks.end()) ? hipSuccess : hipErrorNotReady;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) { return wait_for(g_events[e].marks), hipSuccess; }
+hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { return *t = 0, hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error of the model"; }
+hipError_t hipGetDeviceCount(int* n) { return *n = 1, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { return *p = const_cast<void*>(s), hipSuccess; }
+}
+
+// --- kernels --------------------------------------------------------------------
+namespace nmc {
+void set_next_launch_events(hipEvent_t, hipEvent_t) {}
+bool take_next_launch_events() { return false; }
+#define PASS(name)                                                                              \
+  template <class R>                                                                            \
+  hipError_t name(const FieldTable& ft, PassGeom g, Tables<R> t, hipStream_t s) {               \
+    if (!t.tw) ++g_no_table;                                                                    \
+    return grids(ft, g.nf, s);                                                                  \
+  }
+PASS(launch_fwd_x) PASS(launch_fwd_y) PASS(launch_inv_y) PASS(launch_inv_x) PASS(launch_inv_y_fold)
+PASS(launch_inv_x_fold) PASS(launch_fwd_xy) PASS(launch_inv_yx)
+template <class R>
+hipError_t launch_z(const FieldTable& ft, PassGeom g, Tables<R> t, hipStream_t s) {
+  table(t.gz, cube(g.P, sizeof(R)));
+  table(t.gn, sizeof(R));
+  return grids(ft, g.nf, s);
+}
+template <class R> bool plane_passes_fit(int P) { return P <= 64; }
+#define PLANE(name)                                                                             \
+  template <class R>                                                                            \
+  hipError_t name(const FieldTable& ft, PlaneGeom g, PlaneTables<R> t, hipStream_t s) {         \
+    const int PL = g.plan.C * g.plan.NP;                                                        \
+    if (g.nfull) table(t.gp, cube(PL, sizeof(R))), table(t.tw, PL * 2 * sizeof(R));             \
+    if (g.nbox) {                                                                               \
+      const int PB = g.joint ? PL / 2 : PL;                                                     \
+      table(t.gpb, cube(PB, sizeof(R))), table(t.twb, PB * 2 * sizeof(R));                      \
+    }                                                                                           \
+    return grids(ft, g.nfull + g.nbox, s);                                                      \
+  }
+PLANE(launch_plane_x) PLANE(launch_plane_yz) PLANE(launch_plane_ix) PLANE(launch_plane_ix_box)
+#define SCALED(name)                                                                            \
+  template <class R>                                                                            \
+  hipError_t name(const FieldTable& ft, PlaneGeom g, int S, PlaneTables<R> t, hipStream_t s) {  \
+    const int P = (S + 1) * scaled_points<R>(g.N);                                              \
+    table(t.gp, cube(P, sizeof(R))), table(t.tw, P * 2 * sizeof(R));                            \
+    return grids(ft, g.nfull, s);                                                               \
+  }
+SCALED(launch_scaled_x) SCALED(launch_scaled_yz) SCALED(launch_scaled_ix)
+template <class R>
+hipError_t launch_restrict(const R*, const R*, R* out, int, hipStream_t s) { return op_on(s, {out}); }
+template <class R>
+hipError_t launch_pyramid(const PyramidTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].pyr}); }
+template <class R>
+hipError_t launch_carry(const CarryTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].S}); }
+template <class R>
+hipError_t launch_carry_tri(const CarryTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].S}); }
+template <class R>
+hipError_t launch_accel(const R*, R*, int, int, double, hipStream_t s) { return op_on(s, {}); }
+template <class R>
+hipError_t launch_fft_lines(const void*, void*, int, int, int, const void*, hipStream_t s) { return op_on(s, {}); }
+// tables are read by every later call: only their existence and size is modelled
+hipError_t launch_green(int, double, const double2*, double*, double*, double*, hipStream_t) { return hipSuccess; }
+hipError_t launch_green_sums(int, double, const double2*, double*, double*, hipStream_t) { return hipSuccess; }
+hipError_t launch_round_f32(const double*, float*, size_t, hipStream_t) { return hipSuccess; }
+template <class R>
+hipError_t launch_green_layout(int, const double*, R*, R*, hipStream_t) { return hipSuccess; }
+template <class R>
+hipError_t launch_plane_spectrum(int, int, const double*, R*, hipStream_t) { return hipSuccess; }
+}  // namespace nmc
+
+// --- cases ----------------------------------------------------------------------
+namespace {
+
+int g_failed = 0;
+#define CHECK(c) \
+  do { \
+    if (!(c)) ++g_failed, std::printf("line %d: %s\n", __LINE__, #c); \
+  } while (0)
+
+char* const kRho = (char*)0x10;       // the caller's arrays, outside the model's memory
+char* const kPhi = (char*)(1ull << 40);
+
+hipStream_t stream() {
+  hipStream_t s;
+  (void)hipStreamCreateWithFlags(&s, 0);
+  return s;
+}
+int solve(nmc_ctx* c, int N, int L, hipStream_t s, unsigned flags = 0, nmc_precision p = NMC_F64) {
+  ++g_call;
+  return nmc_solve(c, kRho, kPhi, N, L, 0.1, 2, 1.0, p, flags, s);
+}
+nmc_ctx* context(size_t budget = 0) {
+  nmc_ctx* c = nullptr;
+  CHECK(nmc_create(&c, 0, budget) == NMC_OK);
+  return c;
+}
+void close(nmc_ctx* c) {
+  for (auto& m : g_mem) m.second.in_graph = false;  // the caller's graphs go first
+  nmc_destroy(c);
+  CHECK(g_mem.empty());
+  CHECK(g_races == 0);
+  CHECK(g_no_table == 0);
+}
+
+// A stream's block grows when the stream's handle names another queue than
+// the one whose work still uses it: nobody may get the old block before.
+void outgrown_block() {
+  nmc_ctx* c = context();
+  hipStream_t s = stream();
+  CHECK(solve(c, 64, 1, stream()) == NMC_OK);  // tables
+  CHECK(solve(c, 64, 2, s) == NMC_OK);
+  g_streams[s] = Stream{};                     // destroyed, and given out again
+  CHECK(solve(c, 64, 5, s) == NMC_OK);
+  CHECK(solve(c, 64, 2, stream()) == NMC_OK);
+  close(c);
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const std::map<std::string, void (*)()> cases = {
+      {"outgrown_block", outgrown_block},
+  };
+  if (argc != 2 || !cases.count(argv[1])) return 2;
+  cases.at(argv[1])();
+  std::printf("%s: %s\n", argv[1], g_failed ? "FAILED" : "OK");
+  return g_failed ? 1 : 0;
+}
