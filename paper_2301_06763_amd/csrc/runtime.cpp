@@ -1334,11 +1334,7 @@ int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_
     if (ctx->kept.size() >= kMaxKept) {
       auto lru = std::min_element(ctx->kept.begin(), ctx->kept.end(),
                                   [](const Kept& a, const Kept& b) { return a.used < b.used; });
-      if (lru->ev) (void)hipEventSynchronize(lru->ev);
-      else (void)hipStreamSynchronize(nullptr);
-      if (lru->ev) (void)hipEventDestroy(lru->ev);
-      ctx->free_blocks.push_back(lru->ws);
-      ctx->kept.erase(lru);
+      if ((rc = retire_kept(ctx, lru))) return rc;
     }
     if ((rc = prepare(ctx, N, flags, s, bytes))) return rc;
     Kept k;

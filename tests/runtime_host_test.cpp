@@ -282,11 +282,25 @@ void outgrown_block() {
   close(c);
 }
 
+// More streams than the context keeps workspace for: a solve only enqueues,
+// whatever the streams are still waiting for.
+void many_streams() {
+  nmc_ctx* c = context();
+  CHECK(solve(c, 64, 2, nullptr) == NMC_OK);  // tables; the null stream's block
+  g_waits = 0;
+  std::vector<hipStream_t> s;
+  for (int i = 0; i < 12; ++i) s.push_back(stream());
+  for (int k = 0; k < 36; ++k) CHECK(solve(c, 64, 2, s[k % 12]) == NMC_OK);
+  CHECK(solve(c, 64, 2, nullptr) == NMC_OK);
+  CHECK(g_waits == 0);
+  close(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
-      {"outgrown_block", outgrown_block},
+      {"outgrown_block", outgrown_block}, {"many_streams", many_streams},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
