@@ -149,6 +149,13 @@ int nmc_footprint_bytes_flags(int N, int L, nmc_precision p, unsigned flags, siz
  *         the scaled grids run on a second, library-owned stream that is forked from
  *         and joined back into hip_stream, so completion is ordered on
  *         hip_stream alone.
+ * While hip_stream is being captured into a graph, the call takes workspace of
+ * its own and holds it, like the Green tables it reads, until nmc_destroy (the
+ * graph may be launched at any time; launches of one graph must follow one
+ * another).  The tables must be resident (NMC_EDEVICE otherwise: solve this N
+ * and method once before), and workspace that no cached block serves needs a
+ * capture mode that allows hipMalloc; nmc_solve_noalloc allocates nothing.
+ * The same holds for nmc_solve_batch.
  * Errors: NMC_EINVAL, NMC_EUNSUPPORTED, NMC_ENOMEM, NMC_EDEVICE. */
 int nmc_solve(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, double h0, int refine,
               double G, nmc_precision p, unsigned flags, void* hip_stream);

@@ -179,6 +179,7 @@ struct PerP {
   float *gz32 = nullptr, *gn32 = nullptr;
   size_t bytes = 0;   // device bytes of the spectrum tables held
   uint64_t used = 0;  // last use (context clock), for the LRU eviction
+  bool pinned = false;  // a captured graph reads them: never evicted
 };
 
 // A serving request as the device side needs it: the solve and the event
@@ -227,6 +228,7 @@ struct nmc_ctx {
   char* scratch = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   std::vector<Kept> kept;
+  std::vector<Block> captured;  // workspace of captured solves, held until nmc_destroy
   uint64_t clock = 0;
   // per-pass profiling
   bool profiling = false;
@@ -439,7 +441,8 @@ void reap_leases(nmc_ctx* ctx, bool wait_oldest) {
   while (!ctx->leases.empty()) {
     Lease& l = ctx->leases.front();
     hipError_t q = wait_oldest ? hipEventSynchronize(l.ev) : hipEventQuery(l.ev);
-    if (q == hipErrorNotReady) break;
+    // an event says nothing while its stream is being captured
+    if (q == hipErrorNotReady || q == hipErrorCapturedEvent) break;
     for (auto& b : l.blocks) ctx->free_blocks.push_back(b);
     (void)hipEventDestroy(l.ev);
     ctx->leases.pop_front();
@@ -460,22 +463,24 @@ bool drop_kept(nmc_ctx* ctx) {
   return true;
 }
 
+// The cached block that fits `bytes` best, within 2x; false if none does.
+bool take_free(nmc_ctx* ctx, size_t bytes, Block* out) {
+  int best = -1;
+  for (size_t i = 0; i < ctx->free_blocks.size(); ++i) {
+    const Block& b = ctx->free_blocks[i];
+    if (b.bytes >= bytes && b.bytes < 2 * bytes && (best < 0 || b.bytes < ctx->free_blocks[best].bytes)) best = (int)i;
+  }
+  if (best < 0) return false;
+  *out = ctx->free_blocks[best];
+  ctx->free_blocks.erase(ctx->free_blocks.begin() + best);
+  return true;
+}
+
 int pool_alloc(nmc_ctx* ctx, size_t bytes, Block* out) {
   bytes = align_up(bytes, 2u << 20);
   reap_leases(ctx, false);
   for (int attempt = 0; attempt < 3; ++attempt) {
-    // best fit among cached blocks within 2x
-    int best = -1;
-    for (size_t i = 0; i < ctx->free_blocks.size(); ++i) {
-      const Block& b = ctx->free_blocks[i];
-      if (b.bytes >= bytes && b.bytes < 2 * bytes && (best < 0 || b.bytes < ctx->free_blocks[best].bytes))
-        best = (int)i;
-    }
-    if (best >= 0) {
-      *out = ctx->free_blocks[best];
-      ctx->free_blocks.erase(ctx->free_blocks.begin() + best);
-      return NMC_OK;
-    }
+    if (take_free(ctx, bytes, out)) return NMC_OK;
     // release cached blocks while over budget (or before a fresh allocation fails)
     while (ctx->budget && ctx->allocated + ctx->green_bytes + bytes > ctx->budget && !ctx->free_blocks.empty()) {
       auto it = std::max_element(ctx->free_blocks.begin(), ctx->free_blocks.end(),
@@ -1184,7 +1189,7 @@ void make_room(nmc_ctx* ctx, size_t need, const std::vector<int>& keep) {
     }
     PerP* lru = nullptr;
     for (auto& kv : ctx->perp)
-      if (kv.second.bytes && std::find(keep.begin(), keep.end(), kv.first) == keep.end() &&
+      if (kv.second.bytes && !kv.second.pinned && std::find(keep.begin(), keep.end(), kv.first) == keep.end() &&
           (!lru || kv.second.used < lru->used))
         lru = &kv.second;
     if (!lru) return;
@@ -1272,10 +1277,22 @@ int prepare(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s, size_t ws_bytes)
   return NMC_OK;
 }
 
+// Requests by (N, precision, method), in order inside a group.
+std::map<std::tuple<int, int, int>, std::vector<Req>> group_requests(const Req* reqs, int count) {
+  std::map<std::tuple<int, int, int>, std::vector<Req>> groups;
+  for (int i = 0; i < count; ++i)
+    groups[std::make_tuple(reqs[i].N, (int)reqs[i].p, method_of(reqs[i].flags))].push_back(reqs[i]);
+  return groups;
+}
+size_t group_bytes(const Req* reqs, int count) {  // their workspace
+  size_t n = 0;
+  for (int i = 0; i < count; ++i) n += make_layout(reqs[i].N, reqs[i].L, reqs[i].p, reqs[i].flags).total;
+  return n;
+}
+
 // Launch requests that share N and precision, on one workspace block.
 int launch_group(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s, Lease* lease, hipStream_t aux) {
-  size_t total = 0;
-  for (int i = 0; i < count; ++i) total += make_layout(reqs[i].N, reqs[i].L, reqs[i].p, reqs[i].flags).total;
+  const size_t total = group_bytes(reqs, count);
   int rc = prepare(ctx, reqs[0].N, reqs[0].flags, s, total);
   if (rc) return rc;
   Block b{};
@@ -1284,22 +1301,6 @@ int launch_group(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s, Lease*
   lease->blocks.push_back(b);
   if (reqs[0].p == NMC_F64) return run_group<double>(ctx, reqs, count, (char*)b.ptr, s, aux);
   return run_group<float>(ctx, reqs, count, (char*)b.ptr, s, aux);
-}
-
-int solve_many(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s, Lease* lease) {
-  // group by (N, precision, method), preserving order inside a group
-  std::map<std::tuple<int, int, int>, std::vector<Req>> groups;
-  for (int i = 0; i < count; ++i)
-    groups[std::make_tuple(reqs[i].N, (int)reqs[i].p, method_of(reqs[i].flags))].push_back(reqs[i]);
-  for (auto& kv : groups) {
-    auto& v = kv.second;
-    for (size_t a = 0; a < v.size(); a += kMaxBatchRequests) {
-      const int n = (int)std::min<size_t>(kMaxBatchRequests, v.size() - a);
-      int rc = launch_group(ctx, v.data() + a, n, s, lease, ctx->aux_stream);
-      if (rc) return rc;
-    }
-  }
-  return NMC_OK;
 }
 
 // --- kept workspace -----------------------------------------------------------------
@@ -1360,19 +1361,12 @@ int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_
 // Requests grouped by (N, precision, method), in order inside a group, on the
 // stream's kept workspace, one group after the other.
 int solve_kept(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
-  std::map<std::tuple<int, int, int>, std::vector<Req>> groups;
-  for (int i = 0; i < count; ++i)
-    groups[std::make_tuple(reqs[i].N, (int)reqs[i].p, method_of(reqs[i].flags))].push_back(reqs[i]);
   hipEvent_t done = nullptr;
-  for (auto& kv : groups) {
-    auto& v = kv.second;
+  for (const auto& kv : group_requests(reqs, count)) {
+    const auto& v = kv.second;
     for (size_t a = 0; a < v.size(); a += kMaxBatchRequests) {
       const int n = (int)std::min<size_t>(kMaxBatchRequests, v.size() - a);
-      size_t total = 0;
-      for (int i = 0; i < n; ++i) {
-        const Req& r = v[a + i];
-        total += make_layout(r.N, r.L, r.p, r.flags).total;
-      }
+      const size_t total = group_bytes(v.data() + a, n);
       Kept* k = nullptr;
       int rc = kept_workspace(ctx, v[a].N, v[a].flags, total, s, &k);
       if (rc) return rc;
@@ -1388,28 +1382,62 @@ int solve_kept(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
   return NMC_OK;
 }
 
-// Whether s is being captured: the captured work may run at any later time,
-// so it takes workspace of its own.
+// Whether s is being captured.
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   return s && hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
 }
 
+// The Green tables that a captured solve reads stay where they are until
+// nmc_destroy.
+void pin_tables(nmc_ctx* ctx, int N, unsigned flags) {
+  for (const auto& t : tables_of(N, flags)) ctx->perp[t.P].pinned = true;
+}
+
+// A solve while s is being captured.  The captured work may run whenever its
+// graph is launched and no event says when that has ended, so its workspace
+// (ctx->captured) and the tables it reads are the graph's until nmc_destroy.
+// Nothing here waits or queries an event, which would end the capture (HIP
+// refuses that even for an event recorded on s before): the tables have to be
+// resident, and workspace comes from the cached blocks or a new allocation.
+int solve_captured(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
+  for (const auto& kv : group_requests(reqs, count)) {
+    const auto& v = kv.second;
+    for (size_t a = 0; a < v.size(); a += kMaxBatchRequests) {
+      const int n = (int)std::min<size_t>(kMaxBatchRequests, v.size() - a);
+      for (const auto& t : tables_of(v[a].N, v[a].flags))
+        if (missing_bytes(ctx, t))
+          return fail(ctx, NMC_EDEVICE, "captured solve: the Green tables of period " + std::to_string(t.P) +
+                                            " are not resident (solve this N and method once before the capture)");
+      const size_t bytes = align_up(group_bytes(v.data() + a, n), 2u << 20);
+      Block b{};
+      if (!take_free(ctx, bytes, &b)) {
+        if (ctx->budget && ctx->allocated + ctx->green_bytes + bytes > ctx->budget)
+          return fail(ctx, NMC_ENOMEM, "captured solve: workspace of " + std::to_string(bytes) +
+                                           " bytes does not fit the budget");
+        const hipError_t e = hipMalloc(&b.ptr, bytes);
+        if (e != hipSuccess) {
+          (void)hipGetLastError();
+          return fail(ctx, NMC_ENOMEM, std::string("captured solve: workspace: ") + hipGetErrorString(e));
+        }
+        b.bytes = bytes;
+        ctx->allocated += bytes;
+      }
+      ctx->captured.push_back(b);
+      pin_tables(ctx, v[a].N, v[a].flags);
+      const int rc = v[a].p == NMC_F64 ? run_group<double>(ctx, v.data() + a, n, (char*)b.ptr, s, ctx->aux_stream)
+                                       : run_group<float>(ctx, v.data() + a, n, (char*)b.ptr, s, ctx->aux_stream);
+      if (rc) return rc;
+    }
+  }
+  return NMC_OK;
+}
+
 int solve_on(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
-  int rc;
-  if (!capturing(s)) {
-    rc = solve_kept(ctx, reqs, count, s);
-    if (rc) (void)hipStreamSynchronize(s);  // nothing enqueued before the failure still uses the workspace
-    return rc;
-  }
-  Lease lease;
-  rc = solve_many(ctx, reqs, count, s, &lease);
-  if (rc) {
-    (void)hipStreamSynchronize(s);
-    for (auto& b : lease.blocks) ctx->free_blocks.push_back(b);
-    return rc;
-  }
-  return lease_close(ctx, std::move(lease), s, &ctx->leases);
+  if (capturing(s)) return solve_captured(ctx, reqs, count, s);
+  const int rc = solve_kept(ctx, reqs, count, s);
+  if (rc) (void)hipStreamSynchronize(s);  // nothing enqueued before the failure still uses the workspace
+  return rc;
 }
 
 int set_device(nmc_ctx* ctx) {
@@ -1659,6 +1687,7 @@ void nmc_destroy(nmc_ctx* ctx) {
   for (auto& l : ctx->leases)
     for (auto& blk : l.blocks) (void)hipFree(blk.ptr);
   for (auto& b : ctx->free_blocks) (void)hipFree(b.ptr);
+  for (auto& b : ctx->captured) (void)hipFree(b.ptr);
   if (ctx->arena_base) (void)hipFree(ctx->arena_base);
   for (auto& kv : ctx->perp) {
     free_green(ctx, kv.second);
@@ -1722,6 +1751,7 @@ int nmc_solve_noalloc(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, do
   if (!ctx->scratch) return fail(ctx, NMC_EDEVICE, "nmc_solve_noalloc: no scratch address for this device");
   for (const auto& t : tables_of(N, r.flags)) ctx->perp[t.P].used = ++ctx->clock;
   hipStream_t s = (hipStream_t)hip_stream;
+  if (capturing(s)) pin_tables(ctx, N, r.flags);
   // every grid on the caller's stream; the kernels write every workspace
   // value before reading it, so nothing needs clearing between calls
   return p == NMC_F64 ? run_group<double>(ctx, &r, 1, ctx->scratch, s, s)

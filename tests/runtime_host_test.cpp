@@ -26,7 +26,7 @@ struct Stream {
 };
 struct Event {
   Ops marks;
-  bool captured = false;
+  hipStream_t s = nullptr;
 };
 struct Mem {
   size_t bytes;
@@ -43,7 +43,9 @@ int g_ops = 0, g_call = 0, g_races = 0, g_waits = 0, g_streams_made = 0;
 int g_fail_at = -1;    // launch number (from now) that fails
 int g_mallocs = 0, g_launches = 0;
 
+bool g_ended = false;  // a call that ends a capture
 void wait_for(const Ops& o) {
+  for (const auto& s : g_streams) g_ended |= s.second.capturing;
   if (!std::includes(g_done.begin(), g_done.end(), o.begin(), o.end())) ++g_waits;
   g_done.insert(o.begin(), o.end());
 }
@@ -97,9 +99,10 @@ hipError_t grids(const nmc::FieldTable& ft, int n, hipStream_t s) {
   return hipSuccess;
 }
 int g_no_table = 0;
-void table(const void* p, size_t bytes) {  // a Green table of this size
+void table(const void* p, size_t bytes, hipStream_t s) {  // a Green table of this size
   Mem* m = block_of(p);
   if (!m || m->bytes < bytes) ++g_no_table, std::printf("table missing or of another size (%zu)\n", bytes);
+  else if (g_streams[s].capturing) m->in_graph = true;
 }
 size_t cube(int P, size_t r) { return (size_t)(P / 2 + 1) * (P / 2 + 1) * (P / 2 + 1) * r; }
 
@@ -157,12 +160,12 @@ hipError_t hipEventDestroy(hipEvent_t e) {
   return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-  g_events[e] = Event{g_streams[s].before, g_streams[s].capturing};
+  g_events[e] = Event{g_streams[s].before, s};
   return hipSuccess;
 }
 hipError_t hipEventQuery(hipEvent_t e) {
   const Event& v = g_events[e];
-  if (v.captured) return hipErrorCapturedEvent;
+  if (g_streams[v.s].capturing) return g_ended = true, hipErrorCapturedEvent;  // even if recorded before
   return std::includes(g_done.begin(), g_done.end(), v.marks.begin(), v.marks.end()) ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) { return wait_for(g_events[e].marks), hipSuccess; }
@@ -188,8 +191,8 @@ PASS(launch_fwd_x) PASS(launch_fwd_y) PASS(launch_inv_y) PASS(launch_inv_x) PASS
 PASS(launch_inv_x_fold) PASS(launch_fwd_xy) PASS(launch_inv_yx)
 template <class R>
 hipError_t launch_z(const FieldTable& ft, PassGeom g, Tables<R> t, hipStream_t s) {
-  table(t.gz, cube(g.P, sizeof(R)));
-  table(t.gn, sizeof(R));
+  table(t.gz, cube(g.P, sizeof(R)), s);
+  table(t.gn, sizeof(R), s);
   return grids(ft, g.nf, s);
 }
 template <class R> bool plane_passes_fit(int P) { return P <= 64; }
@@ -197,10 +200,10 @@ template <class R> bool plane_passes_fit(int P) { return P <= 64; }
   template <class R>                                                                            \
   hipError_t name(const FieldTable& ft, PlaneGeom g, PlaneTables<R> t, hipStream_t s) {         \
     const int PL = g.plan.C * g.plan.NP;                                                        \
-    if (g.nfull) table(t.gp, cube(PL, sizeof(R))), table(t.tw, PL * 2 * sizeof(R));             \
+    if (g.nfull) table(t.gp, cube(PL, sizeof(R)), s), table(t.tw, PL * 2 * sizeof(R), s);             \
     if (g.nbox) {                                                                               \
       const int PB = g.joint ? PL / 2 : PL;                                                     \
-      table(t.gpb, cube(PB, sizeof(R))), table(t.twb, PB * 2 * sizeof(R));                      \
+      table(t.gpb, cube(PB, sizeof(R)), s), table(t.twb, PB * 2 * sizeof(R), s);                      \
     }                                                                                           \
     return grids(ft, g.nfull + g.nbox, s);                                                      \
   }
@@ -209,7 +212,7 @@ PLANE(launch_plane_x) PLANE(launch_plane_yz) PLANE(launch_plane_ix) PLANE(launch
   template <class R>                                                                            \
   hipError_t name(const FieldTable& ft, PlaneGeom g, int S, PlaneTables<R> t, hipStream_t s) {  \
     const int P = (S + 1) * scaled_points<R>(g.N);                                              \
-    table(t.gp, cube(P, sizeof(R))), table(t.tw, P * 2 * sizeof(R));                            \
+    table(t.gp, cube(P, sizeof(R)), s), table(t.tw, P * 2 * sizeof(R), s);                            \
     return grids(ft, g.nfull, s);                                                               \
   }
 SCALED(launch_scaled_x) SCALED(launch_scaled_yz) SCALED(launch_scaled_ix)
@@ -296,11 +299,40 @@ void many_streams() {
   close(c);
 }
 
+// A captured call's workspace and tables are the graph's: nobody else gets the
+// block and nothing of it is freed, whatever is solved afterwards.
+void captured() {
+  for (size_t budget : {size_t(0), size_t(24) << 20}) {
+    nmc_ctx* c = context(budget);
+    hipStream_t s = stream();
+    CHECK(solve(c, 16, 3, s) == NMC_OK);
+    (void)hipDeviceSynchronize();
+    for (int graph = 0; graph < 2; ++graph) {
+      if (graph) CHECK(solve(c, 20, 4, s) == NMC_OK);  // the stream's block grows: the old one is still in use
+      g_streams[s].capturing = true;
+      CHECK(solve(c, 16, 3, s) == NMC_OK);
+      if (budget == 0) {  // the call for callers that cannot allocate
+        ++g_call;
+        CHECK(nmc_solve_noalloc(c, kRho, kPhi, 16, 3, 0.1, 2, 1.0, NMC_F32, 0, s) == NMC_OK);
+      }
+      if (budget == 0) CHECK(solve(c, 64, 1, s) == NMC_EDEVICE);  // tables not resident
+      g_streams[s].capturing = false;
+      CHECK(!g_ended);
+    }
+    for (int N : {16, 8, 32, 64, 16, 4, 12, 64, 16})
+      for (int i = 0; i < 3; ++i) {
+        (void)hipDeviceSynchronize();
+        CHECK(solve(c, N, N == 64 ? 1 : 3, i ? stream() : s) == NMC_OK);
+      }
+    close(c);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
-      {"outgrown_block", outgrown_block}, {"many_streams", many_streams},
+      {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
