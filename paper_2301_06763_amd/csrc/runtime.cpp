@@ -1436,7 +1436,12 @@ int solve_captured(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
 int solve_on(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
   if (capturing(s)) return solve_captured(ctx, reqs, count, s);
   const int rc = solve_kept(ctx, reqs, count, s);
-  if (rc) (void)hipStreamSynchronize(s);  // nothing enqueued before the failure still uses the workspace
+  if (rc) {
+    // nothing enqueued before the failure still uses the workspace: s, and the
+    // second stream if the failure came between its fork and its join
+    (void)hipStreamSynchronize(s);
+    (void)hipStreamSynchronize(ctx->aux_stream);
+  }
   return rc;
 }
 

@@ -328,11 +328,33 @@ void captured() {
   }
 }
 
+// A launch fails at any point of a solve, also after the second stream has been
+// forked: the next solve is not beside what that one left behind.
+void failed_launch() {
+  struct { int N, L; unsigned flags; } const shapes[] = {{128, 3, 0}, {64, 3, NMC_MODIFIED3}, {256, 2, NMC_MODIFIED}};
+  nmc_ctx* c = context();
+  for (auto q : shapes) {
+    hipStream_t s = stream();
+    CHECK(solve(c, q.N, q.L, s, q.flags) == NMC_OK);
+    const int before = g_launches;
+    CHECK(solve(c, q.N, q.L, s, q.flags) == NMC_OK);
+    const int n = g_launches - before;
+    for (int k = 0; k < n; ++k) {
+      g_fail_at = k;
+      CHECK(solve(c, q.N, q.L, s, q.flags) == NMC_EDEVICE);
+      CHECK(g_fail_at == -1);
+      CHECK(solve(c, q.N, q.L, s, q.flags) == NMC_OK);
+    }
+  }
+  close(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
+      {"failed_launch", failed_launch},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
