@@ -479,7 +479,7 @@ bool take_free(nmc_ctx* ctx, size_t bytes, Block* out) {
 int pool_alloc(nmc_ctx* ctx, size_t bytes, Block* out) {
   bytes = align_up(bytes, 2u << 20);
   reap_leases(ctx, false);
-  for (int attempt = 0; attempt < 3; ++attempt) {
+  for (;;) {
     if (take_free(ctx, bytes, out)) return NMC_OK;
     // release cached blocks while over budget (or before a fresh allocation fails)
     while (ctx->budget && ctx->allocated + ctx->green_bytes + bytes > ctx->budget && !ctx->free_blocks.empty()) {
@@ -512,10 +512,11 @@ int pool_alloc(nmc_ctx* ctx, size_t bytes, Block* out) {
       }
       (void)hipGetLastError();
     }
-    // wait for the oldest outstanding solve, or take back the kept
-    // workspace of the streams, then retry
-    if (!ctx->leases.empty()) reap_leases(ctx, true);
-    else if (!drop_kept(ctx)) break;
+    // wait for the oldest outstanding solve, then, with none left, take back
+    // the kept workspace of the streams, and retry
+    const size_t outstanding = ctx->leases.size();
+    if (outstanding) reap_leases(ctx, true);
+    if (ctx->leases.size() == outstanding && !drop_kept(ctx)) break;
   }
   return fail(ctx, NMC_ENOMEM, "workspace of " + std::to_string(bytes) + " bytes does not fit (budget " +
                                    std::to_string(ctx->budget) + "; held: " + std::to_string(ctx->allocated) +

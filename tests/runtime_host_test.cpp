@@ -349,12 +349,33 @@ void failed_launch() {
   close(c);
 }
 
+// The device has room for one large workspace: a call that needs it waits for
+// every lease and takes back what is kept for other streams.
+void device_full() {
+  nmc_ctx* c = context();
+  CHECK(solve(c, 64, 5, stream()) == NMC_OK);  // tables
+  std::vector<hipStream_t> s;
+  for (int i = 0; i < 4; ++i) s.push_back(stream());
+  for (int L : {1, 2, 4})  // outgrown blocks: leases; and one kept for each stream
+    for (hipStream_t q : s) CHECK(solve(c, 64, L, q) == NMC_OK);
+  g_capacity = g_held;
+  size_t tables = 0;
+  for (const auto& m : g_mem)
+    if (m.second.uses.empty()) tables += m.second.bytes;
+  size_t ws = 0;
+  CHECK(nmc_footprint_bytes(64, 16, NMC_F64, &ws) == NMC_OK);
+  CHECK(ws + tables + (4 << 20) < g_capacity);  // it fits, alone
+  CHECK(solve(c, 64, 16, stream()) == NMC_OK);
+  g_capacity = ~size_t(0);
+  close(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
-      {"failed_launch", failed_launch},
+      {"failed_launch", failed_launch}, {"device_full", device_full},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
