@@ -215,8 +215,9 @@ int nmc_solve_batch(nmc_ctx* ctx, const nmc_request* reqs, int count, void* hip_
  * batched solve on the next serving stream, so new work overlaps the work
  * already on the device.  Under a budget the batches' workspace comes from
  * one device allocation made at the first serving launch (what the budget
- * leaves beside the Green tables, the workspace of solves in flight and a
- * sixteenth of the budget, at most 1 GiB, kept for tables of other periods)
+ * leaves beside the Green tables, the workspace of solves in flight, that kept
+ * for the streams of solves (unless the allocation would get less than it) and
+ * a sixteenth of the budget, at most 1 GiB, kept for tables of other periods)
  * and used as a ring, so a serving loop at its budget makes no allocation,
  * free or device-wide wait; a batch that does not fit beside the batches in
  * flight waits for the next tick, and one larger than the whole ring (with

@@ -1489,20 +1489,29 @@ int scratch_address(nmc_ctx* ctx, int dev, char** out) {
 // and completes with an event recorded after it.
 // The serving arena of a context with a budget: created at the first
 // serving launch from what the budget leaves beside the Green tables, the
-// workspace of solves in flight and room for the tables of other periods
-// (a sixteenth of the budget, at most 1 GiB); cached solve workspace blocks
-// are released first.  make_room frees it again while no batch uses it.
+// workspace of solves in flight, that kept for the streams of solves and room
+// for the tables of other periods (a sixteenth of the budget, at most 1 GiB);
+// cached solve workspace blocks are released first.  The kept workspace stays,
+// so that the same solves run beside batches in flight, unless the arena would
+// get less than it.  make_room frees the arena again while no batch uses it.
 int ensure_arena(nmc_ctx* ctx) {
   if (ctx->arena_base) return NMC_OK;
-  drop_kept(ctx);
-  reap_leases(ctx, false);
-  for (auto& b : ctx->free_blocks) {
-    (void)hipFree(b.ptr);
-    ctx->allocated -= b.bytes;
-  }
-  ctx->free_blocks.clear();
+  auto release_cached = [&] {
+    reap_leases(ctx, false);
+    for (auto& b : ctx->free_blocks) {
+      (void)hipFree(b.ptr);
+      ctx->allocated -= b.bytes;
+    }
+    ctx->free_blocks.clear();
+  };
+  release_cached();
   const size_t headroom = std::min<size_t>(ctx->budget / 16, size_t(1) << 30);
-  const size_t held = ctx->allocated + ctx->green_bytes + headroom;
+  size_t held = ctx->allocated + ctx->green_bytes + headroom, kept = 0;
+  for (const auto& k : ctx->kept) kept += k.ws.bytes;
+  if (held + kept > ctx->budget && drop_kept(ctx)) {
+    release_cached();
+    held = ctx->allocated + ctx->green_bytes + headroom;
+  }
   if (held >= ctx->budget) return fail(ctx, NMC_ENOMEM, "serving: the budget leaves no room for serving workspace");
   const size_t size = (ctx->budget - held) / (2u << 20) * (2u << 20);
   void* p = nullptr;

@@ -370,12 +370,40 @@ void device_full() {
   close(c);
 }
 
+int submit(nmc_ctx* c, int N, int L, hipStream_t s) {
+  const nmc_request q{kRho, kPhi, N, L, 0.1, 1.0, NMC_F64, 0};
+  uint64_t t;
+  ++g_call;
+  return nmc_serve_submit(c, &q, s, &t);
+}
+
+// Solves beside batches in flight under a budget: the stream's workspace is
+// still there, unless the serving arena would get less than it.
+void beside_serving() {
+  for (bool large : {false, true}) {
+    nmc_ctx* c = context((large ? 300 : 800) << 20ull);
+    hipStream_t s = stream();
+    for (int k = 0; k < 2; ++k) CHECK(solve(c, 64, 6, s) == NMC_OK);  // 140 MB
+    CHECK(submit(c, 64, 3, s) == NMC_OK);
+    int launched = 0;
+    CHECK(nmc_serve_tick(c, &launched) == NMC_OK && launched == 1);
+    nmc_serve_stats st;
+    CHECK(nmc_serve_stats_get(c, &st) == NMC_OK && st.inflight == 1);
+    if (!large) CHECK(solve(c, 64, 6, s) == NMC_OK);
+    else CHECK(st.arena_bytes > 250u << 20);
+    CHECK(nmc_serve_drain(c) == NMC_OK);
+    CHECK(solve(c, 64, 6, s) == NMC_OK);
+    close(c);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
       {"failed_launch", failed_launch}, {"device_full", device_full},
+      {"beside_serving", beside_serving},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
