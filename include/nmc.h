@@ -82,8 +82,8 @@ enum {
   /* Use the separate X, Y, Z, I2 and I1 passes even where passes that keep a
    * plane in LDS apply (N <= 32: one XY and one I2+I1 launch per kind of grid;
    * levels of up to 96 cells, FP32 128, boxes and scaled grids: X, YZ, IX).  For
-   * ablation.  In a batch, ONE_STREAM and NO_FUSED_PLANES are taken from the
-   * first request of each group of equal N, precision and method. */
+   * ablation.  In a batch, ONE_STREAM is taken from the first request of each
+   * group of equal N, precision, method and NO_FUSED_PLANES. */
   NMC_NO_FUSED_PLANES = 1u << 5,
   /* The modified convolution method of Sect. 7 and Appendix B (Eqs. B.1,
    * B.2), which keeps the dipole moments between neighbouring levels: for
@@ -201,8 +201,8 @@ typedef struct {
 
 /* Solve `count` independent nested meshes (Sect. 4: the grids of a solve are
  * independent, and so are solves).  Requests of equal N, precision and
- * method (original, NMC_MODIFIED, NMC_MODIFIED3; and carry rule) share
- * every FFT pass launch.  Each result is bitwise identical to the same request solved
+ * method (original, NMC_MODIFIED, NMC_MODIFIED3; carry rule and
+ * NMC_NO_FUSED_PLANES) share every FFT pass launch.  Each result is bitwise identical to the same request solved
  * alone.  All requests are validated before any work. */
 int nmc_solve_batch(nmc_ctx* ctx, const nmc_request* reqs, int count, void* hip_stream);
 
@@ -211,7 +211,7 @@ int nmc_solve_batch(nmc_ctx* ctx, const nmc_request* reqs, int count, void* hip_
  * finished batches (returning their workspace), then admits queued requests
  * in arrival order while the summed nmc_footprint_bytes of in-flight work
  * stays within the budget, groups the admitted ones as nmc_solve_batch does
- * (N, precision, method and carry rule) and launches each group as one
+ * (N, precision, method, carry rule and NO_FUSED_PLANES) and launches each group as one
  * batched solve on the next serving stream, so new work overlaps the work
  * already on the device.  Under a budget the batches' workspace comes from
  * one device allocation made at the first serving launch (what the budget

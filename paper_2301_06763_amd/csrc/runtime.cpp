@@ -63,10 +63,11 @@ bool is_modified(unsigned flags) { return (flags & (NMC_MODIFIED | NMC_MODIFIED3
 // per level with two finer levels.
 bool is_modified3(unsigned flags, int L) { return (flags & NMC_MODIFIED3) != 0 && L >= 3; }
 // Which method a request uses (requests of one group share every launch):
-// original / modified / three-level, times two carry rules.
+// original / modified / three-level, times two carry rules, times the passes
+// that NMC_NO_FUSED_PLANES asks for.
 int method_of(unsigned flags) {
   const int m = (flags & NMC_MODIFIED3) ? 2 : (flags & NMC_MODIFIED) ? 1 : 0;
-  return m + ((flags & NMC_PROLONG_TRILINEAR) ? 3 : 0);
+  return m + ((flags & NMC_PROLONG_TRILINEAR) ? 3 : 0) + ((flags & NMC_NO_FUSED_PLANES) ? 6 : 0);
 }
 // Largest period a solve with these flags needs.
 int max_period(int N, int L, unsigned flags) {

@@ -90,8 +90,10 @@ hipError_t op_on(hipStream_t s, std::initializer_list<const void*> bufs) {
   g_streams[s].before.insert(op);
   return hipSuccess;
 }
-hipError_t grids(const nmc::FieldTable& ft, int n, hipStream_t s) {
+std::map<std::string, int> g_passes;  // grids per pass
+hipError_t grids(const char* pass, const nmc::FieldTable& ft, int n, hipStream_t s) {
   ++g_launches;
+  g_passes[pass] += n;
   if (g_fail_at >= 0 && g_fail_at-- == 0) return hipErrorLaunchFailure;
   const int op = g_ops++;
   for (int i = 0; i < n; ++i) use(ft.f[i].A, s, op), use(ft.f[i].B, s, op);
@@ -185,7 +187,7 @@ bool take_next_launch_events() { return false; }
   template <class R>                                                                            \
   hipError_t name(const FieldTable& ft, PassGeom g, Tables<R> t, hipStream_t s) {               \
     if (!t.tw) ++g_no_table;                                                                    \
-    return grids(ft, g.nf, s);                                                                  \
+    return grids(#name, ft, g.nf, s);                                                           \
   }
 PASS(launch_fwd_x) PASS(launch_fwd_y) PASS(launch_inv_y) PASS(launch_inv_x) PASS(launch_inv_y_fold)
 PASS(launch_inv_x_fold) PASS(launch_fwd_xy) PASS(launch_inv_yx)
@@ -193,7 +195,7 @@ template <class R>
 hipError_t launch_z(const FieldTable& ft, PassGeom g, Tables<R> t, hipStream_t s) {
   table(t.gz, cube(g.P, sizeof(R)), s);
   table(t.gn, sizeof(R), s);
-  return grids(ft, g.nf, s);
+  return grids("launch_z", ft, g.nf, s);
 }
 template <class R> bool plane_passes_fit(int P) { return P <= 64; }
 #define PLANE(name)                                                                             \
@@ -205,7 +207,7 @@ template <class R> bool plane_passes_fit(int P) { return P <= 64; }
       const int PB = g.joint ? PL / 2 : PL;                                                     \
       table(t.gpb, cube(PB, sizeof(R)), s), table(t.twb, PB * 2 * sizeof(R), s);                      \
     }                                                                                           \
-    return grids(ft, g.nfull + g.nbox, s);                                                      \
+    return grids(#name, ft, g.nfull + g.nbox, s);                                               \
   }
 PLANE(launch_plane_x) PLANE(launch_plane_yz) PLANE(launch_plane_ix) PLANE(launch_plane_ix_box)
 #define SCALED(name)                                                                            \
@@ -213,7 +215,7 @@ PLANE(launch_plane_x) PLANE(launch_plane_yz) PLANE(launch_plane_ix) PLANE(launch
   hipError_t name(const FieldTable& ft, PlaneGeom g, int S, PlaneTables<R> t, hipStream_t s) {  \
     const int P = (S + 1) * scaled_points<R>(g.N);                                              \
     table(t.gp, cube(P, sizeof(R)), s), table(t.tw, P * 2 * sizeof(R), s);                            \
-    return grids(ft, g.nfull, s);                                                               \
+    return grids(#name, ft, g.nfull, s);                                                        \
   }
 SCALED(launch_scaled_x) SCALED(launch_scaled_yz) SCALED(launch_scaled_ix)
 template <class R>
@@ -397,13 +399,42 @@ void beside_serving() {
   }
 }
 
+// Requests of one call take the passes that each takes alone, whichever comes
+// first (results are bitwise those of the solve alone).
+void mixed_batch() {
+  nmc_ctx* c = context();
+  hipStream_t s = stream();
+  for (unsigned method : {0u, (unsigned)NMC_MODIFIED})
+    for (int N : {16, 64, 128}) {
+      const unsigned flags[2] = {method, method | NMC_NO_FUSED_PLANES};
+      g_passes.clear();
+      for (unsigned f : flags) CHECK(solve(c, N, 2, s, f) == NMC_OK);
+      const auto alone = g_passes;
+      for (int first : {0, 1}) {
+        nmc_request q[2];
+        for (int i = 0; i < 2; ++i) q[i] = {kRho, kPhi, N, 2, 0.1, 1.0, NMC_F64, flags[i ^ first]};
+        g_passes.clear();
+        ++g_call;
+        CHECK(nmc_solve_batch(c, q, 2, s) == NMC_OK);
+        CHECK(g_passes == alone);
+        uint64_t t;
+        g_passes.clear();
+        for (auto& r : q) CHECK(nmc_serve_submit(c, &r, s, &t) == NMC_OK);
+        ++g_call;
+        CHECK(nmc_serve_drain(c) == NMC_OK);
+        CHECK(g_passes == alone);
+      }
+    }
+  close(c);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> cases = {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
       {"failed_launch", failed_launch}, {"device_full", device_full},
-      {"beside_serving", beside_serving},
+      {"beside_serving", beside_serving}, {"mixed_batch", mixed_batch},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();
