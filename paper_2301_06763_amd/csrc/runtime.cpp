@@ -75,6 +75,25 @@ int max_period(int N, int L, unsigned flags) {
   return is_modified3(flags, L) ? 4 * P : is_modified(flags) ? 2 * P : P;
 }
 
+// The passes that a mesh of N cells takes in precision R.
+struct Route {
+  bool planes;     // levels plane by plane on plan (plane.hip), boxes with them
+  bool boxes;      // the passes of kernels.hip with child-region boxes, else with hole grids
+  bool box_planes; // these boxes plane by plane on box_plan
+  int scaled;      // scaled grids plane by plane, points per class (plane_scaled.hip); 0: passes at 2P, 4P
+  nmc::PlanePlan plan, box_plan;
+};
+template <class R>
+Route route_of(int N, unsigned flags) {
+  Route r{};
+  const bool separate = (flags & NMC_NO_FUSED_PLANES) != 0, mod = is_modified(flags);
+  r.planes = !separate && nmc::plane_plan<R>(N, &r.plan);
+  r.boxes = use_boxes(N) && !mod && !r.planes;
+  r.box_planes = r.boxes && !separate && nmc::plane_box_plan<R>(period_of(N) / 2, &r.box_plan);
+  r.scaled = mod && !separate ? nmc::scaled_points<R>(N) : 0;
+  return r;
+}
+
 // Workspace layout of one request (offsets from its base): per level l the
 // full grid's A and B; per level l < L-1 the second grid (hole grid,
 // child-region box, or with the modified method the doubled grid), the
@@ -303,7 +322,7 @@ double self_cell_integral() {
 // The tables hang on a public period (nmc_period of N, or twice or four times
 // it for scaled grids), where the diagnostic's octant is also kept.
 struct TableNeed {
-  int P;              // public period
+  int P = 0;          // public period
   bool z64 = false, z32 = false;
   struct Plane {
     int period;
@@ -643,15 +662,10 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
   const int P = period_of(N);
   const int NC = N / 2 + 2;
   const bool mod = is_modified(reqs[0].flags);
-  // all grids plane by plane (plane.hip), or the passes of kernels.hip, there
-  // with child-region boxes (boxes) or hole grids; the boxes again plane by
-  // plane where they fit (box_planes)
-  nmc::PlanePlan plan{}, box_plan{};
-  const bool separate = (reqs[0].flags & NMC_NO_FUSED_PLANES) != 0;
-  const bool planes = !separate && nmc::plane_plan<R>(N, &plan);
-  const int NPS = mod && !separate ? nmc::scaled_points<R>(N) : 0;  // scaled grids plane by plane
-  const bool boxes = use_boxes(N) && !mod && !planes;
-  const bool box_planes = boxes && !separate && nmc::plane_box_plan<R>(P / 2, &box_plan);
+  const Route route = route_of<R>(N, reqs[0].flags);
+  const nmc::PlanePlan plan = route.plan, box_plan = route.box_plan;
+  const bool planes = route.planes, boxes = route.boxes, box_planes = route.box_planes;
+  const int NPS = route.scaled;
   const int PL = planes ? plan.C * plan.NP : P;  // period of the levels
   const int PB = PL / 2;                         // and of the child-region boxes
   const int PD = 2 * P;  // period of the doubled grids (modified method)
@@ -1007,7 +1021,7 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
   };
   int rc;
   const bool one_stream = (reqs[0].flags & NMC_ONE_STREAM) != 0;
-  const bool fused = nmc::plane_passes_fit<R>(P) && !separate;
+  const bool fused = nmc::plane_passes_fit<R>(P) && !(reqs[0].flags & NMC_NO_FUSED_PLANES);
   if (planes && !mod) {
     // every grid shares the X and YZ launches; the hole potentials (Phi^l - C,
     // or a hole grid's own) on the stencil boxes, the carry cascade, then the
@@ -1199,49 +1213,45 @@ void make_room(nmc_ctx* ctx, size_t need, const std::vector<int>& keep) {
   }
 }
 
+// Adds what a solve of N cells with these flags reads in precision R.
+template <class R>
+void add_tables(std::vector<TableNeed>& need, int N, unsigned flags) {
+  const int P = period_of(N);
+  const bool f64 = sizeof(R) == 8;
+  const Route r = route_of<R>(N, flags);
+  auto of = [&](int period) -> TableNeed& {
+    for (auto& t : need)
+      if (t.P == period) return t;
+    need.push_back({period});
+    return need.back();
+  };
+  auto z = [&](int period) { (f64 ? of(period).z64 : of(period).z32) = true; };
+  auto plane = [&](int period) {  // hung on P
+    for (auto& q : of(P).planes)
+      if (q.period == period) return (void)((f64 ? q.f64 : q.f32) = true);
+    of(P).planes.push_back({period, f64, !f64});
+  };
+  const bool mod = is_modified(flags), m3 = (flags & NMC_MODIFIED3) && 4 * P <= kMaxScaledP;
+  if (r.planes) plane(r.plan.C * r.plan.NP);
+  else z(P);
+  if (r.planes && !mod) plane(r.plan.C * r.plan.NP / 2);  // their boxes
+  if (r.box_planes) plane(P / 2);
+  else if (r.boxes) z(P / 2);
+  if (mod)
+    for (int S : {2, 4}) {
+      if (S == 4 && !m3) continue;
+      if (r.scaled) plane((S + 1) * r.scaled);
+      else z(S * P);
+    }
+}
+
 // The Green tables of every period a solve of N cells with these flags reads,
 // in both precisions (a later call of either finds them).
 std::vector<TableNeed> tables_of(int N, unsigned flags) {
-  const int P = period_of(N);
   std::vector<TableNeed> need;
-  if (is_modified(flags)) {
-    // the levels' tables, then the scaled grids': plane by plane per precision
-    // where they have a size for it, else the z passes at 2P and 4P
-    const bool m3 = (flags & NMC_MODIFIED3) && 4 * P <= kMaxScaledP;
-    const bool separate = (flags & NMC_NO_FUSED_PLANES) != 0;
-    const int n64 = separate ? 0 : nmc::scaled_points<double>(N), n32 = separate ? 0 : nmc::scaled_points<float>(N);
-    nmc::PlanePlan p64{}, p32{};
-    const bool l64 = !separate && nmc::plane_plan<double>(N, &p64), l32 = !separate && nmc::plane_plan<float>(N, &p32);
-    TableNeed t{P, !l64, !l32, {}};
-    if (l64) t.planes.push_back({p64.C * p64.NP, true, false});
-    if (l32) t.planes.push_back({p32.C * p32.NP, false, true});
-    for (int c : {3, 5}) {
-      if (c == 5 && !m3) continue;
-      if (n64) t.planes.push_back({c * n64, true, false});
-      if (n32) t.planes.push_back({c * n32, false, true});
-    }
-    need.push_back(t);
-    for (int q : {2 * P, 4 * P})
-      if ((q == 2 * P || m3) && (!n64 || !n32)) need.push_back({q, !n64, !n32, {}});
-    return need;
-  }
-  const bool separate = (flags & NMC_NO_FUSED_PLANES) != 0;
-  TableNeed t{P, separate, separate, {}};
-  auto add = [&](int period, bool f64, bool f32) {
-    if (f64 || f32) t.planes.push_back({period, f64, f32});
-  };
-  nmc::PlanePlan p64, p32;
-  const bool on64 = nmc::plane_plan<double>(N, &p64), on32 = nmc::plane_plan<float>(N, &p32);
-  t.z64 = t.z64 || !on64;
-  t.z32 = t.z32 || !on32;
-  if (on64) add(p64.C * p64.NP, true, on32);
-  else if (on32) add(p32.C * p32.NP, false, true);
-  if (on64) add(p64.C * p64.NP / 2, true, on32);
-  else add(P / 2, nmc::plane_box_plan<double>(P / 2, &p64), nmc::plane_box_plan<float>(P / 2, &p32));
-  need.push_back(t);
-  // the boxes of the separate passes: half the period, where no plane pass takes them
-  if (use_boxes(N) && (separate || !nmc::plane_box_plan<double>(P / 2, &p64)))
-    need.push_back({P / 2, true, separate, {}});
+  need.push_back({period_of(N)});
+  add_tables<double>(need, N, flags);
+  add_tables<float>(need, N, flags);
   return need;
 }
 
@@ -1907,8 +1917,11 @@ int nmc_green_spectrum(nmc_ctx* ctx, int N, nmc_precision p, void* out, void* hi
   // and those of N/2 and N/4 theirs of the scaled grids on up to four times
   // their period
   for (int n : {N / 2, N / 4})
-    if (n >= kMinN && n % 4 == 0 && N <= 256 && n <= 64)
-      for (const auto& t : tables_of(n, n == N / 2 ? NMC_MODIFIED : NMC_MODIFIED3)) tables.push_back(t);
+    if (n >= kMinN && n % 4 == 0 && n <= 64) {
+      const unsigned method = n == N / 2 ? NMC_MODIFIED : NMC_MODIFIED3;
+      add_tables<double>(tables, n, method);
+      add_tables<float>(tables, n, method);
+    }
   if ((rc = prepare_tables(ctx, tables, s))) return rc;
   const size_t H = P / 2 + 1, n = H * H * H;
   PerP& pp = ctx->perp[P];

@@ -32,6 +32,7 @@ struct Mem {
   size_t bytes;
   std::vector<std::pair<int, int>> uses;  // (operation, call)
   bool in_graph = false;
+  bool table = false, read = false;  // a Green table, and one that a launch has read
 };
 std::map<hipStream_t, Stream> g_streams;
 std::map<hipEvent_t, Event> g_events;
@@ -104,7 +105,14 @@ int g_no_table = 0;
 void table(const void* p, size_t bytes, hipStream_t s) {  // a Green table of this size
   Mem* m = block_of(p);
   if (!m || m->bytes < bytes) ++g_no_table, std::printf("table missing or of another size (%zu)\n", bytes);
-  else if (g_streams[s].capturing) m->in_graph = true;
+  else {
+    m->read = true;
+    if (g_streams[s].capturing) m->in_graph = true;
+  }
+}
+hipError_t build_table(const void* p) {
+  if (Mem* m = block_of(p)) m->table = true;
+  return hipSuccess;
 }
 size_t cube(int P, size_t r) { return (size_t)(P / 2 + 1) * (P / 2 + 1) * (P / 2 + 1) * r; }
 
@@ -117,7 +125,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (g_held + n > g_capacity) return hipErrorOutOfMemory;
   g_held += n;
   *p = g_next;
-  g_mem[g_next] = Mem{n, {}, false};
+  g_mem[g_next] = Mem{n, {}};
   g_next += (n + 4095) / 4096 * 4096 + 4096;
   return hipSuccess;
 }
@@ -235,9 +243,9 @@ hipError_t launch_green(int, double, const double2*, double*, double*, double*, 
 hipError_t launch_green_sums(int, double, const double2*, double*, double*, hipStream_t) { return hipSuccess; }
 hipError_t launch_round_f32(const double*, float*, size_t, hipStream_t) { return hipSuccess; }
 template <class R>
-hipError_t launch_green_layout(int, const double*, R*, R*, hipStream_t) { return hipSuccess; }
+hipError_t launch_green_layout(int, const double*, R* gz, R*, hipStream_t) { return build_table(gz); }
 template <class R>
-hipError_t launch_plane_spectrum(int, int, const double*, R*, hipStream_t) { return hipSuccess; }
+hipError_t launch_plane_spectrum(int, int, const double*, R* gp, hipStream_t) { return build_table(gp); }
 }  // namespace nmc
 
 // --- cases ----------------------------------------------------------------------
@@ -263,6 +271,11 @@ int solve(nmc_ctx* c, int N, int L, hipStream_t s, unsigned flags = 0, nmc_preci
 }
 nmc_ctx* context(size_t budget = 0) {
   nmc_ctx* c = nullptr;
+  if (g_mem.empty()) {  // nothing is left of earlier contexts
+    g_ops = 0;
+    g_done.clear();
+    g_streams.clear();
+  }
   CHECK(nmc_create(&c, 0, budget) == NMC_OK);
   return c;
 }
@@ -428,6 +441,23 @@ void mixed_batch() {
   close(c);
 }
 
+// Every size, method and choice of passes finds the tables that its launches
+// read, in both precisions, and no other is built for it.
+void tables() {
+  for (int N = 4; N <= 256; N += 4)
+    for (unsigned method : {0u, (unsigned)NMC_MODIFIED, (unsigned)NMC_MODIFIED3})
+      for (unsigned f : {method, method | NMC_NO_FUSED_PLANES, method | NMC_NO_RESTRICT}) {
+        if (method == NMC_MODIFIED3 && N > 128) continue;
+        nmc_ctx* c = context();
+        for (nmc_precision p : {NMC_F64, NMC_F32}) CHECK(solve(c, N, 3, nullptr, f, p) == NMC_OK);
+        bool all = true;
+        for (const auto& m : g_mem) all = all && (!m.second.table || m.second.read);
+        // (kept coarse densities: the boxes' tables serve the other meshes of a batch)
+        if (!all && !(f & NMC_NO_RESTRICT)) ++g_failed, std::printf("N %d flags %u: a table nobody reads\n", N, f);
+        close(c);
+      }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -435,6 +465,7 @@ int main(int argc, char** argv) {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
       {"failed_launch", failed_launch}, {"device_full", device_full},
       {"beside_serving", beside_serving}, {"mixed_batch", mixed_batch},
+      {"tables", tables},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();

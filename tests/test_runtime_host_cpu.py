@@ -10,7 +10,7 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving", "mixed_batch"]
+CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving", "mixed_batch", "tables"]
 
 
 @pytest.fixture(scope="module")
