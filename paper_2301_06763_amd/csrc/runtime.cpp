@@ -455,6 +455,31 @@ void free_green(nmc_ctx* ctx, PerP& pp) {
   pp.bytes = 0;
 }
 
+// Of a public period's tables, those that `need` does not name; false if there
+// are none.
+bool free_unread(nmc_ctx* ctx, const TableNeed& need) {
+  PerP& pp = ctx->perp[need.P];
+  if (pp.pinned) return false;
+  const size_t before = pp.bytes;
+  auto drop = [&](auto** p, size_t bytes) {
+    if (!*p) return;
+    (void)hipFree(*p);
+    *p = nullptr;
+    pp.bytes -= bytes;
+  };
+  if (!need.z64) drop(&pp.gz64, cube_bytes(need.P, 8)), pp.gn64 = nullptr;
+  if (!need.z32) drop(&pp.gz32, cube_bytes(need.P, 4)), pp.gn32 = nullptr;
+  for (auto& [period, t] : pp.planes) {
+    TableNeed::Plane q{period, false, false};
+    for (const auto& n : need.planes)
+      if (n.period == period) q = n;
+    if (!q.f64) drop(&t.gp64, cube_bytes(period, 8));
+    if (!q.f32) drop(&t.gp32, cube_bytes(period, 4));
+  }
+  ctx->green_bytes -= before - pp.bytes;
+  return pp.bytes != before;
+}
+
 // --- workspace pool ------------------------------------------------------------
 
 void reap_leases(nmc_ctx* ctx, bool wait_oldest) {
@@ -1176,9 +1201,10 @@ void release_arena(nmc_ctx* ctx) {
 
 // Under a budget, until `need` more bytes fit: release cached workspace
 // blocks, then the streams' kept workspace, then the least recently used
-// Green tables whose period is not in `keep` (after the device has finished every use).  What still does not
-// fit is reported by the allocation that follows.
-void make_room(nmc_ctx* ctx, size_t need, const std::vector<int>& keep) {
+// Green tables of periods that `keep` does not name, then those of its periods
+// that only other sizes read (after the device has finished every use).  What
+// still does not fit is reported by the allocation that follows.
+void make_room(nmc_ctx* ctx, size_t need, const std::vector<TableNeed>& keep) {
   if (!ctx->budget) return;
   auto over = [&] { return ctx->allocated + ctx->green_bytes + need > ctx->budget; };
   bool synced = false;
@@ -1205,11 +1231,15 @@ void make_room(nmc_ctx* ctx, size_t need, const std::vector<int>& keep) {
     }
     PerP* lru = nullptr;
     for (auto& kv : ctx->perp)
-      if (kv.second.bytes && !kv.second.pinned && std::find(keep.begin(), keep.end(), kv.first) == keep.end() &&
+      if (kv.second.bytes && !kv.second.pinned &&
+          std::none_of(keep.begin(), keep.end(), [&](const TableNeed& t) { return t.P == kv.first; }) &&
           (!lru || kv.second.used < lru->used))
         lru = &kv.second;
-    if (!lru) return;
-    free_green(ctx, *lru);
+    if (lru) {
+      free_green(ctx, *lru);
+      continue;
+    }
+    if (std::none_of(keep.begin(), keep.end(), [&](const TableNeed& t) { return free_unread(ctx, t); })) return;
   }
 }
 
@@ -1255,18 +1285,11 @@ std::vector<TableNeed> tables_of(int N, unsigned flags) {
   return need;
 }
 
-std::vector<int> periods_of(const std::vector<TableNeed>& need) {
-  std::vector<int> keep;
-  for (const auto& t : need) keep.push_back(t.P);
-  return keep;
-}
-
 // The Green tables (and twiddles) of every period a group needs.
 int prepare_tables(nmc_ctx* ctx, const std::vector<TableNeed>& tables, hipStream_t s) {
-  const std::vector<int> keep = periods_of(tables);
   size_t need = 0;
   for (const auto& t : tables) need += missing_bytes(ctx, t);
-  if (need) make_room(ctx, need, keep);
+  if (need) make_room(ctx, need, tables);
   for (const auto& t : tables) {
     int rc = ensure_green(ctx, t, s);
     if (rc) return rc;
@@ -1279,13 +1302,12 @@ int prepare(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s, size_t ws_bytes)
   const std::vector<TableNeed> tables = tables_of(N, flags);
   int rc = prepare_tables(ctx, tables, s);
   if (rc) return rc;
-  const std::vector<int> keep = periods_of(tables);
   // a cached block the pool will reuse for the workspace needs no room
   const size_t ws = align_up(ws_bytes, 2u << 20);
   reap_leases(ctx, false);
   const bool reusable = std::any_of(ctx->free_blocks.begin(), ctx->free_blocks.end(),
                                     [&](const Block& b) { return b.bytes >= ws && b.bytes < 2 * ws; });
-  if (!reusable) make_room(ctx, ws, keep);
+  if (!reusable) make_room(ctx, ws, tables);
   return NMC_OK;
 }
 

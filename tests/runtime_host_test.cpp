@@ -458,6 +458,30 @@ void tables() {
       }
 }
 
+// A budget of the workspace and of what the tables of the periods took when
+// every size of a period shared them (24 bytes a point) is enough, for one size
+// after another.
+void tight_budget() {
+  for (int first : {16, 32, 48, 64, 96, 100, 128, 200, 256})
+    for (unsigned f : {0u, (unsigned)NMC_NO_FUSED_PLANES, (unsigned)NMC_MODIFIED, (unsigned)NMC_MODIFIED3}) {
+      if (f == NMC_MODIFIED3 && first > 128) continue;
+      const int P = period_of(first), other = first == P / 2 ? P / 4 + 4 : P / 2;
+      size_t ws = 0, more = 0;
+      CHECK(nmc_footprint_bytes_flags(first, 3, NMC_F64, f, &ws) == NMC_OK);
+      CHECK(nmc_footprint_bytes_flags(other, 3, NMC_F64, f, &more) == NMC_OK);
+      size_t budget = align_up(std::max(ws, more), 2u << 20) + cube(P, 24);
+      if (is_modified(f)) budget += cube(2 * P, 24);
+      if (f == NMC_MODIFIED3) budget += cube(4 * P, 24);
+      nmc_ctx* c = context(budget);
+      for (int N : {first, first, other, first}) {
+        for (nmc_precision p : {NMC_F64, NMC_F32})
+          if (solve(c, N, 3, nullptr, f, p) != NMC_OK) ++g_failed, std::printf("N %d flags %u refused\n", N, f);
+        CHECK(g_held <= budget + (8 << 20));  // the twiddles are not counted
+      }
+      close(c);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -465,7 +489,7 @@ int main(int argc, char** argv) {
       {"outgrown_block", outgrown_block}, {"many_streams", many_streams}, {"captured", captured},
       {"failed_launch", failed_launch}, {"device_full", device_full},
       {"beside_serving", beside_serving}, {"mixed_batch", mixed_batch},
-      {"tables", tables},
+      {"tables", tables}, {"tight_budget", tight_budget},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();

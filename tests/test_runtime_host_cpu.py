@@ -10,7 +10,8 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving", "mixed_batch", "tables"]
+CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving",
+         "mixed_batch", "tables", "tight_budget"]
 
 
 @pytest.fixture(scope="module")
