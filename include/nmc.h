@@ -179,7 +179,10 @@ int nmc_solve(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, double h0,
  *   with NMC_MODIFIED / NMC_MODIFIED3) must already be resident in ctx, built
  *   by an earlier nmc_solve of the same N and method or by nmc_green_spectrum
  *   of that N (and 2N, 4N); a table evicted under the context's budget must be
- *   rebuilt the same way.
+ *   rebuilt the same way.  A solve leaves the tables of the separate passes
+ *   beside those of its own where the budget has room, so a solve of another
+ *   N or method with the same periods does too; where only the tables of the
+ *   other choice of NMC_NO_FUSED_PLANES are resident, those passes run.
  * Errors: as nmc_solve; NMC_ENOMEM when the workspace
  * (nmc_footprint_bytes_flags) exceeds NMC_SCRATCH_BYTES or a table is not
  * resident (nothing is enqueued then). */

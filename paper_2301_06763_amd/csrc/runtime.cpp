@@ -1199,50 +1199,6 @@ void release_arena(nmc_ctx* ctx) {
   ctx->arena = nmc::RingArena{};
 }
 
-// Under a budget, until `need` more bytes fit: release cached workspace
-// blocks, then the streams' kept workspace, then the least recently used
-// Green tables of periods that `keep` does not name, then those of its periods
-// that only other sizes read (after the device has finished every use).  What
-// still does not fit is reported by the allocation that follows.
-void make_room(nmc_ctx* ctx, size_t need, const std::vector<TableNeed>& keep) {
-  if (!ctx->budget) return;
-  auto over = [&] { return ctx->allocated + ctx->green_bytes + need > ctx->budget; };
-  bool synced = false;
-  reap_leases(ctx, false);
-  while (over()) {
-    if (!ctx->free_blocks.empty()) {
-      auto it = std::max_element(ctx->free_blocks.begin(), ctx->free_blocks.end(),
-                                 [](const Block& a, const Block& b) { return a.bytes < b.bytes; });
-      (void)hipFree(it->ptr);
-      ctx->allocated -= it->bytes;
-      ctx->free_blocks.erase(it);
-      continue;
-    }
-    if (ctx->arena_base && ctx->arena.empty() && (!ctx->serve || ctx->serve->idle())) {
-      release_arena(ctx);  // the serving arena, while no batch uses it
-      continue;
-    }
-    if (!synced) {
-      (void)hipDeviceSynchronize();
-      reap_leases(ctx, false);
-      drop_kept(ctx);
-      synced = true;
-      continue;  // completed leases and the kept workspace are free now
-    }
-    PerP* lru = nullptr;
-    for (auto& kv : ctx->perp)
-      if (kv.second.bytes && !kv.second.pinned &&
-          std::none_of(keep.begin(), keep.end(), [&](const TableNeed& t) { return t.P == kv.first; }) &&
-          (!lru || kv.second.used < lru->used))
-        lru = &kv.second;
-    if (lru) {
-      free_green(ctx, *lru);
-      continue;
-    }
-    if (std::none_of(keep.begin(), keep.end(), [&](const TableNeed& t) { return free_unread(ctx, t); })) return;
-  }
-}
-
 // Adds what a solve of N cells with these flags reads in precision R.
 template <class R>
 void add_tables(std::vector<TableNeed>& need, int N, unsigned flags) {
@@ -1285,12 +1241,93 @@ std::vector<TableNeed> tables_of(int N, unsigned flags) {
   return need;
 }
 
-// The Green tables (and twiddles) of every period a group needs.
-int prepare_tables(nmc_ctx* ctx, const std::vector<TableNeed>& tables, hipStream_t s) {
-  size_t need = 0;
-  for (const auto& t : tables) need += missing_bytes(ctx, t);
-  if (need) make_room(ctx, need, tables);
+// The tables of a call: those it reads, and spare ones that are built with them
+// while there is room beside what is held.
+struct TablePlan {
+  std::vector<TableNeed> read, spare;
+  size_t shared = 0;  // what tables of the separate passes alone take on its periods
+  static bool in(const std::vector<TableNeed>& v, int P) {
+    return std::any_of(v.begin(), v.end(), [&](const TableNeed& t) { return t.P == P; });
+  }
+  bool reads(int P) const { return in(read, P); }
+  bool names(int P) const { return in(read, P) || in(spare, P); }
+};
+
+// A solve's.  Spare: the tables of the separate passes on its periods (P; 2P and
+// 4P with the modified methods), with which any nmc_solve_noalloc on these
+// periods can run, whatever its size, method and choice of passes; up to period
+// 256, above which no workspace fits the static scratch.
+TablePlan solve_tables(int N, unsigned flags) {
+  TablePlan plan;
+  plan.read = tables_of(N, flags);
+  for (int q = period_of(N), k = 1; k <= 4; q *= 2, k *= 2) {
+    if ((k > 1 && !is_modified(flags)) || (k > 2 && !(flags & NMC_MODIFIED3)) || q > kMaxScaledP) break;
+    plan.shared += cube_bytes(q, 24);
+    if (q <= 256) plan.spare.push_back({q, true, true, {}});
+  }
+  return plan;
+}
+
+// Under a budget, until `need` more bytes fit: release cached workspace
+// blocks, then the streams' kept workspace, then the least recently used
+// Green tables of periods that the plan does not name, then the plan's spare
+// ones and those of its periods that only other sizes read; these before the
+// others once the plan's periods hold more than plan.shared (after the device
+// has finished every use).  What still does not fit is reported by the
+// allocation that follows.
+void make_room(nmc_ctx* ctx, size_t need, const TablePlan& plan) {
+  if (!ctx->budget) return;
+  auto over = [&] { return ctx->allocated + ctx->green_bytes + need > ctx->budget; };
+  bool synced = false;
+  reap_leases(ctx, false);
+  while (over()) {
+    if (!ctx->free_blocks.empty()) {
+      auto it = std::max_element(ctx->free_blocks.begin(), ctx->free_blocks.end(),
+                                 [](const Block& a, const Block& b) { return a.bytes < b.bytes; });
+      (void)hipFree(it->ptr);
+      ctx->allocated -= it->bytes;
+      ctx->free_blocks.erase(it);
+      continue;
+    }
+    if (ctx->arena_base && ctx->arena.empty() && (!ctx->serve || ctx->serve->idle())) {
+      release_arena(ctx);  // the serving arena, while no batch uses it
+      continue;
+    }
+    if (!synced) {
+      (void)hipDeviceSynchronize();
+      reap_leases(ctx, false);
+      drop_kept(ctx);
+      synced = true;
+      continue;  // completed leases and the kept workspace are free now
+    }
+    auto drop_spare = [&] {
+      bool any = false;
+      for (const auto& t : plan.read) any = free_unread(ctx, t) || any;
+      for (const auto& t : plan.spare) {
+        PerP& pp = ctx->perp[t.P];
+        if (plan.reads(t.P) || !pp.bytes || pp.pinned) continue;
+        free_green(ctx, pp);
+        any = true;
+      }
+      return any;
+    };
+    size_t held = 0;
+    PerP* lru = nullptr;
+    for (auto& [period, pp] : ctx->perp) {
+      if (plan.names(period)) held += pp.bytes;
+      else if (pp.bytes && !pp.pinned && (!lru || pp.used < lru->used)) lru = &pp;
+    }
+    if ((held > plan.shared || !lru) && drop_spare()) continue;
+    if (!lru) return;
+    free_green(ctx, *lru);
+  }
+}
+
+// Builds the tables that fit beside what is held.
+int build_spare(nmc_ctx* ctx, const std::vector<TableNeed>& tables, hipStream_t s) {
   for (const auto& t : tables) {
+    const size_t n = missing_bytes(ctx, t);
+    if (!n || (ctx->budget && ctx->allocated + ctx->green_bytes + n > ctx->budget)) continue;
     int rc = ensure_green(ctx, t, s);
     if (rc) return rc;
     ctx->perp[t.P].used = ++ctx->clock;
@@ -1298,16 +1335,39 @@ int prepare_tables(nmc_ctx* ctx, const std::vector<TableNeed>& tables, hipStream
   return NMC_OK;
 }
 
+// The Green tables (and twiddles) of a plan; the spare ones when some of those
+// that the call reads had to be built.
+int prepare_tables(nmc_ctx* ctx, const TablePlan& plan, hipStream_t s) {
+  size_t need = 0;
+  for (const auto& t : plan.read) need += missing_bytes(ctx, t);
+  if (need) make_room(ctx, need, plan);
+  for (const auto& t : plan.read) {
+    int rc = ensure_green(ctx, t, s);
+    if (rc) return rc;
+    ctx->perp[t.P].used = ++ctx->clock;
+  }
+  return need ? build_spare(ctx, plan.spare, s) : NMC_OK;
+}
+int prepare_tables(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s) {
+  bool missing = false;
+  for (const auto& t : tables_of(N, flags)) {
+    missing = missing || missing_bytes(ctx, t);
+    ctx->perp[t.P].used = ++ctx->clock;
+  }
+  return missing ? prepare_tables(ctx, solve_tables(N, flags), s) : NMC_OK;
+}
+
+// Tables and room for a workspace of ws_bytes, under the budget.
 int prepare(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s, size_t ws_bytes) {
-  const std::vector<TableNeed> tables = tables_of(N, flags);
-  int rc = prepare_tables(ctx, tables, s);
+  const TablePlan plan = solve_tables(N, flags);
+  int rc = prepare_tables(ctx, plan, s);
   if (rc) return rc;
   // a cached block the pool will reuse for the workspace needs no room
   const size_t ws = align_up(ws_bytes, 2u << 20);
   reap_leases(ctx, false);
   const bool reusable = std::any_of(ctx->free_blocks.begin(), ctx->free_blocks.end(),
                                     [&](const Block& b) { return b.bytes >= ws && b.bytes < 2 * ws; });
-  if (!reusable) make_room(ctx, ws, tables);
+  if (!reusable) make_room(ctx, ws, plan);
   return NMC_OK;
 }
 
@@ -1358,7 +1418,7 @@ int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_
   auto of_stream = [&] {
     return std::find_if(ctx->kept.begin(), ctx->kept.end(), [&](const Kept& k) { return k.s == s; });
   };
-  int rc = prepare_tables(ctx, tables_of(N, flags), s);  // may drop the kept workspace
+  int rc = prepare_tables(ctx, N, flags, s);  // may drop the kept workspace
   if (rc) return rc;
   auto it = of_stream();
   if (it != ctx->kept.end() && it->ws.bytes < bytes) {
@@ -1582,7 +1642,7 @@ class HipServeDevice final : public nmc::ServeDevice {
     if (ctx_->budget) {
       for (const Req& r : rs) arena_bytes += make_layout(r.N, r.L, r.p, r.flags).total;
       arena_bytes = align_up(arena_bytes, size_t(64) << 10);
-      if ((rc = prepare_tables(ctx_, tables_of(rs[0].N, rs[0].flags), s))) return rc;
+      if ((rc = prepare_tables(ctx_, rs[0].N, rs[0].flags, s))) return rc;
       if ((rc = ensure_arena(ctx_))) return rc == NMC_ENOMEM ? NMC_EDEVICE : rc;
       if (ctx_->arena.alloc(arena_bytes, &arena_off)) {
         lease->in_arena = true;
@@ -1780,21 +1840,30 @@ int nmc_solve_noalloc(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, do
     return fail(ctx, NMC_ENOMEM, "nmc_solve_noalloc: workspace of " + std::to_string(need) +
                                      " bytes exceeds the static scratch of " + std::to_string(NMC_SCRATCH_BYTES) +
                                      " bytes");
-  // every table the solve reads must already be resident: building one allocates
-  // (NMC_NO_FUSED_PLANES is dropped where only the plane passes' tables are)
-  auto missing = [&](unsigned f) {
-    if (is_modified(f) && !is_modified3(f, L)) f = (f & ~(unsigned)NMC_MODIFIED3) | NMC_MODIFIED;
-    for (const auto& t : tables_of(N, f)) {
+  // every table the solve reads must already be resident: building one allocates.
+  // Where those of the passes asked for are not, but those of the other choice
+  // of NMC_NO_FUSED_PLANES are, these run.
+  unsigned f = flags;
+  if (is_modified(f) && !is_modified3(f, L)) f = (f & ~(unsigned)NMC_MODIFIED3) | NMC_MODIFIED;
+  if (L == 1) f &= ~(unsigned)NMC_MODIFIED;  // no scaled grids
+  auto missing = [&](unsigned g) {
+    std::vector<TableNeed> tables;
+    if (p == NMC_F64) add_tables<double>(tables, N, g);
+    else add_tables<float>(tables, N, g);
+    for (const auto& t : tables) {
+      if (L == 1 && t.P < period_of(N)) continue;  // no boxes
       auto it = ctx->perp.find(t.P);
       if (it == ctx->perp.end() || !it->second.tw64 || missing_bytes(ctx, t)) return t.P;
     }
     return 0;
   };
-  if (!is_modified(flags) && missing(flags)) r.flags &= ~(unsigned)NMC_NO_FUSED_PLANES;
-  if (const int P = missing(r.flags))
-    return fail(ctx, NMC_ENOMEM, "nmc_solve_noalloc: the Green tables of period " + std::to_string(P) +
-                                     " are not resident (build them first with nmc_solve or "
-                                     "nmc_green_spectrum of this N and method)");
+  if (const int P = missing(f)) {
+    if (missing(f ^ NMC_NO_FUSED_PLANES))
+      return fail(ctx, NMC_ENOMEM, "nmc_solve_noalloc: the Green tables of period " + std::to_string(P) +
+                                       " are not resident (build them first with nmc_solve or "
+                                       "nmc_green_spectrum of this N and method)");
+    r.flags ^= NMC_NO_FUSED_PLANES;
+  }
   if ((rc = set_device(ctx))) return rc;
   if (!ctx->scratch) return fail(ctx, NMC_EDEVICE, "nmc_solve_noalloc: no scratch address for this device");
   for (const auto& t : tables_of(N, r.flags)) ctx->perp[t.P].used = ++ctx->clock;
@@ -1934,17 +2003,21 @@ int nmc_green_spectrum(nmc_ctx* ctx, int N, nmc_precision p, void* out, void* hi
   hipStream_t s = (hipStream_t)hip_stream;
   // the tables count against the budget like those of a solve
   // (every solve of this N finds its tables afterwards, nmc_solve_noalloc)
-  std::vector<TableNeed> tables = tables_of(N, 0);
-  tables[0].z64 = tables[0].z32 = true;
-  // and those of N/2 and N/4 theirs of the scaled grids on up to four times
-  // their period
+  TablePlan plan;
+  plan.read = tables_of(N, 0);
+  plan.read[0].z64 = plan.read[0].z32 = true;
+  plan.shared = cube_bytes(P, 24);
+  if ((rc = prepare_tables(ctx, plan, s))) return rc;
+  // and N/2 and N/4 theirs of the scaled grids on up to four times their
+  // period, where there is room
+  std::vector<TableNeed> scaled;
   for (int n : {N / 2, N / 4})
     if (n >= kMinN && n % 4 == 0 && n <= 64) {
       const unsigned method = n == N / 2 ? NMC_MODIFIED : NMC_MODIFIED3;
-      add_tables<double>(tables, n, method);
-      add_tables<float>(tables, n, method);
+      add_tables<double>(scaled, n, method);
+      add_tables<float>(scaled, n, method);
     }
-  if ((rc = prepare_tables(ctx, tables, s))) return rc;
+  if ((rc = build_spare(ctx, scaled, s))) return rc;
   const size_t H = P / 2 + 1, n = H * H * H;
   PerP& pp = ctx->perp[P];
   pp.used = ++ctx->clock;

@@ -32,7 +32,7 @@ struct Mem {
   size_t bytes;
   std::vector<std::pair<int, int>> uses;  // (operation, call)
   bool in_graph = false;
-  bool table = false, read = false;  // a Green table, and one that a launch has read
+  bool table = false, read = false;  // a table of the plane passes, and one that a launch has read
 };
 std::map<hipStream_t, Stream> g_streams;
 std::map<hipEvent_t, Event> g_events;
@@ -243,7 +243,7 @@ hipError_t launch_green(int, double, const double2*, double*, double*, double*, 
 hipError_t launch_green_sums(int, double, const double2*, double*, double*, hipStream_t) { return hipSuccess; }
 hipError_t launch_round_f32(const double*, float*, size_t, hipStream_t) { return hipSuccess; }
 template <class R>
-hipError_t launch_green_layout(int, const double*, R* gz, R*, hipStream_t) { return build_table(gz); }
+hipError_t launch_green_layout(int, const double*, R*, R*, hipStream_t) { return hipSuccess; }
 template <class R>
 hipError_t launch_plane_spectrum(int, int, const double*, R* gp, hipStream_t) { return build_table(gp); }
 }  // namespace nmc
@@ -442,7 +442,7 @@ void mixed_batch() {
 }
 
 // Every size, method and choice of passes finds the tables that its launches
-// read, in both precisions, and no other is built for it.
+// read, in both precisions, and no plane table is built that none of them reads.
 void tables() {
   for (int N = 4; N <= 256; N += 4)
     for (unsigned method : {0u, (unsigned)NMC_MODIFIED, (unsigned)NMC_MODIFIED3})
@@ -456,6 +456,52 @@ void tables() {
         if (!all && !(f & NMC_NO_RESTRICT)) ++g_failed, std::printf("N %d flags %u: a table nobody reads\n", N, f);
         close(c);
       }
+}
+
+// nmc_solve_noalloc of a mesh finds its tables after any call that leaves
+// those of its periods (P, and 2P and 4P of the modified methods): a solve of
+// another size, method, precision or choice of passes, or nmc_green_spectrum.
+void noalloc_tables() {
+  struct Call { int N; unsigned flags; bool spectrum; };
+  const unsigned M = NMC_MODIFIED, M3 = NMC_MODIFIED3, S = NMC_NO_FUSED_PLANES;
+  std::vector<Call> calls;
+  for (int N : {8, 16, 20, 32, 36, 48, 64, 68, 96, 100, 124, 128, 256}) {
+    for (unsigned f : {0u, S, M, M | S, M3, M3 | S})
+      if (N <= 128 || !is_modified(f)) calls.push_back({N, f, false});
+    calls.push_back({N, 0, true});
+  }
+  auto periods = [](int N, unsigned f, bool m3) {
+    const int P = period_of(N);
+    std::set<int> o{P};
+    if (is_modified(f)) o.insert(2 * P);
+    if (m3) o.insert(4 * P);
+    return o;
+  };
+  int accepted = 0;
+  for (const Call& x : calls) {
+    nmc_ctx* c = context();
+    if (x.spectrum) CHECK(nmc_green_spectrum(c, x.N, NMC_F32, kPhi, nullptr) == NMC_OK);
+    else CHECK(solve(c, x.N, 3, nullptr, x.flags) == NMC_OK);
+    const auto left = periods(x.N, x.flags, (x.flags & M3) != 0);
+    for (const Call& y : calls)
+      for (int L : {1, 2, 3})
+        for (nmc_precision p : {NMC_F64, NMC_F32}) {
+          if (y.spectrum) continue;
+          size_t ws = 0;
+          if (nmc_footprint_bytes_flags(y.N, L, p, y.flags, &ws) != NMC_OK || ws > NMC_SCRATCH_BYTES) continue;
+          const auto need = periods(y.N, y.flags, is_modified3(y.flags, L));
+          if (!std::includes(left.begin(), left.end(), need.begin(), need.end())) continue;
+          ++g_call;
+          ++accepted;
+          const int mallocs = g_mallocs;
+          if (nmc_solve_noalloc(c, kRho, kPhi, y.N, L, 0.1, 2, 1.0, p, y.flags, nullptr) != NMC_OK)
+            ++g_failed, std::printf("after %s %d flags %u: N %d L %d flags %u precision %d refused\n",
+                                    x.spectrum ? "spectrum" : "solve", x.N, x.flags, y.N, L, y.flags, (int)p);
+          CHECK(mallocs == g_mallocs);
+        }
+    close(c);
+  }
+  CHECK(accepted > 500);
 }
 
 // A budget of the workspace and of what the tables of the periods took when
@@ -490,6 +536,7 @@ int main(int argc, char** argv) {
       {"failed_launch", failed_launch}, {"device_full", device_full},
       {"beside_serving", beside_serving}, {"mixed_batch", mixed_batch},
       {"tables", tables}, {"tight_budget", tight_budget},
+      {"noalloc_tables", noalloc_tables},
   };
   if (argc != 2 || !cases.count(argv[1])) return 2;
   cases.at(argv[1])();

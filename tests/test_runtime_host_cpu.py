@@ -10,8 +10,8 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
-CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving",
-         "mixed_batch", "tables", "tight_budget"]
+CASES = ["outgrown_block", "many_streams", "captured", "failed_launch", "device_full", "beside_serving", "mixed_batch", "tables", "tight_budget",
+         "noalloc_tables"]
 
 
 @pytest.fixture(scope="module")
