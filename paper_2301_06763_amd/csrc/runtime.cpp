@@ -1199,9 +1199,10 @@ void release_arena(nmc_ctx* ctx) {
   ctx->arena = nmc::RingArena{};
 }
 
-// Adds what a solve of N cells with these flags reads in precision R.
+// Adds what a solve of N cells with these flags reads in precision R, of public
+// periods up to `limit` and plane passes up to 5/4 of it.
 template <class R>
-void add_tables(std::vector<TableNeed>& need, int N, unsigned flags) {
+void add_tables(std::vector<TableNeed>& need, int N, unsigned flags, int limit) {
   const int P = period_of(N);
   const bool f64 = sizeof(R) == 8;
   const Route r = route_of<R>(N, flags);
@@ -1211,8 +1212,11 @@ void add_tables(std::vector<TableNeed>& need, int N, unsigned flags) {
     need.push_back({period});
     return need.back();
   };
-  auto z = [&](int period) { (f64 ? of(period).z64 : of(period).z32) = true; };
+  auto z = [&](int period) {
+    if (period <= limit) (f64 ? of(period).z64 : of(period).z32) = true;
+  };
   auto plane = [&](int period) {  // hung on P
+    if (P > limit || 4 * period > 5 * limit) return;
     for (auto& q : of(P).planes)
       if (q.period == period) return (void)((f64 ? q.f64 : q.f32) = true);
     of(P).planes.push_back({period, f64, !f64});
@@ -1232,12 +1236,14 @@ void add_tables(std::vector<TableNeed>& need, int N, unsigned flags) {
 }
 
 // The Green tables of every period a solve of N cells with these flags reads,
-// in both precisions (a later call of either finds them).
-std::vector<TableNeed> tables_of(int N, unsigned flags) {
+// and those of the other precision (nmc_solve_noalloc of either finds them) up to
+// period 256, above which no workspace fits the static scratch.
+constexpr int kNoallocP = 256;
+std::vector<TableNeed> tables_of(int N, unsigned flags, nmc_precision p) {
   std::vector<TableNeed> need;
   need.push_back({period_of(N)});
-  add_tables<double>(need, N, flags);
-  add_tables<float>(need, N, flags);
+  add_tables<double>(need, N, flags, p == NMC_F64 ? kMaxScaledP : kNoallocP);
+  add_tables<float>(need, N, flags, p == NMC_F32 ? kMaxScaledP : kNoallocP);
   return need;
 }
 
@@ -1257,13 +1263,13 @@ struct TablePlan {
 // 4P with the modified methods), with which any nmc_solve_noalloc on these
 // periods can run, whatever its size, method and choice of passes; up to period
 // 256, above which no workspace fits the static scratch.
-TablePlan solve_tables(int N, unsigned flags) {
+TablePlan solve_tables(int N, unsigned flags, nmc_precision p) {
   TablePlan plan;
-  plan.read = tables_of(N, flags);
+  plan.read = tables_of(N, flags, p);
   for (int q = period_of(N), k = 1; k <= 4; q *= 2, k *= 2) {
     if ((k > 1 && !is_modified(flags)) || (k > 2 && !(flags & NMC_MODIFIED3)) || q > kMaxScaledP) break;
     plan.shared += cube_bytes(q, 24);
-    if (q <= 256) plan.spare.push_back({q, true, true, {}});
+    if (q <= kNoallocP) plan.spare.push_back({q, true, true, {}});
   }
   return plan;
 }
@@ -1348,18 +1354,18 @@ int prepare_tables(nmc_ctx* ctx, const TablePlan& plan, hipStream_t s) {
   }
   return need ? build_spare(ctx, plan.spare, s) : NMC_OK;
 }
-int prepare_tables(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s) {
+int prepare_tables(nmc_ctx* ctx, int N, unsigned flags, nmc_precision p, hipStream_t s) {
   bool missing = false;
-  for (const auto& t : tables_of(N, flags)) {
+  for (const auto& t : tables_of(N, flags, p)) {
     missing = missing || missing_bytes(ctx, t);
     ctx->perp[t.P].used = ++ctx->clock;
   }
-  return missing ? prepare_tables(ctx, solve_tables(N, flags), s) : NMC_OK;
+  return missing ? prepare_tables(ctx, solve_tables(N, flags, p), s) : NMC_OK;
 }
 
 // Tables and room for a workspace of ws_bytes, under the budget.
-int prepare(nmc_ctx* ctx, int N, unsigned flags, hipStream_t s, size_t ws_bytes) {
-  const TablePlan plan = solve_tables(N, flags);
+int prepare(nmc_ctx* ctx, int N, unsigned flags, nmc_precision p, hipStream_t s, size_t ws_bytes) {
+  const TablePlan plan = solve_tables(N, flags, p);
   int rc = prepare_tables(ctx, plan, s);
   if (rc) return rc;
   // a cached block the pool will reuse for the workspace needs no room
@@ -1387,7 +1393,7 @@ size_t group_bytes(const Req* reqs, int count) {  // their workspace
 // Launch requests that share N and precision, on one workspace block.
 int launch_group(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s, Lease* lease, hipStream_t aux) {
   const size_t total = group_bytes(reqs, count);
-  int rc = prepare(ctx, reqs[0].N, reqs[0].flags, s, total);
+  int rc = prepare(ctx, reqs[0].N, reqs[0].flags, reqs[0].p, s, total);
   if (rc) return rc;
   Block b{};
   rc = pool_alloc(ctx, total, &b);
@@ -1414,11 +1420,11 @@ int retire_kept(nmc_ctx* ctx, std::vector<Kept>::iterator k) {
 
 // Workspace of `bytes` for solves on stream s, ordered after the stream's
 // earlier ones; *out is valid until the next call that may allocate.
-int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_t s, Kept** out) {
+int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, nmc_precision p, size_t bytes, hipStream_t s, Kept** out) {
   auto of_stream = [&] {
     return std::find_if(ctx->kept.begin(), ctx->kept.end(), [&](const Kept& k) { return k.s == s; });
   };
-  int rc = prepare_tables(ctx, N, flags, s);  // may drop the kept workspace
+  int rc = prepare_tables(ctx, N, flags, p, s);  // may drop the kept workspace
   if (rc) return rc;
   auto it = of_stream();
   if (it != ctx->kept.end() && it->ws.bytes < bytes) {
@@ -1431,7 +1437,7 @@ int kept_workspace(nmc_ctx* ctx, int N, unsigned flags, size_t bytes, hipStream_
                                   [](const Kept& a, const Kept& b) { return a.used < b.used; });
       if ((rc = retire_kept(ctx, lru))) return rc;
     }
-    if ((rc = prepare(ctx, N, flags, s, bytes))) return rc;
+    if ((rc = prepare(ctx, N, flags, p, s, bytes))) return rc;
     Kept k;
     k.s = s;
     if (s) {
@@ -1462,7 +1468,7 @@ int solve_kept(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
       const int n = (int)std::min<size_t>(kMaxBatchRequests, v.size() - a);
       const size_t total = group_bytes(v.data() + a, n);
       Kept* k = nullptr;
-      int rc = kept_workspace(ctx, v[a].N, v[a].flags, total, s, &k);
+      int rc = kept_workspace(ctx, v[a].N, v[a].flags, v[a].p, total, s, &k);
       if (rc) return rc;
       char* const ws = (char*)k->ws.ptr;
       done = k->ev;
@@ -1484,8 +1490,8 @@ bool capturing(hipStream_t s) {
 
 // The Green tables that a captured solve reads stay where they are until
 // nmc_destroy.
-void pin_tables(nmc_ctx* ctx, int N, unsigned flags) {
-  for (const auto& t : tables_of(N, flags)) ctx->perp[t.P].pinned = true;
+void pin_tables(nmc_ctx* ctx, int N, unsigned flags, nmc_precision p) {
+  for (const auto& t : tables_of(N, flags, p)) ctx->perp[t.P].pinned = true;
 }
 
 // A solve while s is being captured.  The captured work may run whenever its
@@ -1499,7 +1505,7 @@ int solve_captured(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
     const auto& v = kv.second;
     for (size_t a = 0; a < v.size(); a += kMaxBatchRequests) {
       const int n = (int)std::min<size_t>(kMaxBatchRequests, v.size() - a);
-      for (const auto& t : tables_of(v[a].N, v[a].flags))
+      for (const auto& t : tables_of(v[a].N, v[a].flags, v[a].p))
         if (missing_bytes(ctx, t))
           return fail(ctx, NMC_EDEVICE, "captured solve: the Green tables of period " + std::to_string(t.P) +
                                             " are not resident (solve this N and method once before the capture)");
@@ -1518,7 +1524,7 @@ int solve_captured(nmc_ctx* ctx, const Req* reqs, int count, hipStream_t s) {
         ctx->allocated += bytes;
       }
       ctx->captured.push_back(b);
-      pin_tables(ctx, v[a].N, v[a].flags);
+      pin_tables(ctx, v[a].N, v[a].flags, v[a].p);
       const int rc = v[a].p == NMC_F64 ? run_group<double>(ctx, v.data() + a, n, (char*)b.ptr, s, ctx->aux_stream)
                                        : run_group<float>(ctx, v.data() + a, n, (char*)b.ptr, s, ctx->aux_stream);
       if (rc) return rc;
@@ -1642,7 +1648,7 @@ class HipServeDevice final : public nmc::ServeDevice {
     if (ctx_->budget) {
       for (const Req& r : rs) arena_bytes += make_layout(r.N, r.L, r.p, r.flags).total;
       arena_bytes = align_up(arena_bytes, size_t(64) << 10);
-      if ((rc = prepare_tables(ctx_, rs[0].N, rs[0].flags, s))) return rc;
+      if ((rc = prepare_tables(ctx_, rs[0].N, rs[0].flags, rs[0].p, s))) return rc;
       if ((rc = ensure_arena(ctx_))) return rc == NMC_ENOMEM ? NMC_EDEVICE : rc;
       if (ctx_->arena.alloc(arena_bytes, &arena_off)) {
         lease->in_arena = true;
@@ -1848,8 +1854,8 @@ int nmc_solve_noalloc(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, do
   if (L == 1) f &= ~(unsigned)NMC_MODIFIED;  // no scaled grids
   auto missing = [&](unsigned g) {
     std::vector<TableNeed> tables;
-    if (p == NMC_F64) add_tables<double>(tables, N, g);
-    else add_tables<float>(tables, N, g);
+    if (p == NMC_F64) add_tables<double>(tables, N, g, kMaxScaledP);
+    else add_tables<float>(tables, N, g, kMaxScaledP);
     for (const auto& t : tables) {
       if (L == 1 && t.P < period_of(N)) continue;  // no boxes
       auto it = ctx->perp.find(t.P);
@@ -1866,9 +1872,9 @@ int nmc_solve_noalloc(nmc_ctx* ctx, const void* rho, void* phi, int N, int L, do
   }
   if ((rc = set_device(ctx))) return rc;
   if (!ctx->scratch) return fail(ctx, NMC_EDEVICE, "nmc_solve_noalloc: no scratch address for this device");
-  for (const auto& t : tables_of(N, r.flags)) ctx->perp[t.P].used = ++ctx->clock;
+  for (const auto& t : tables_of(N, r.flags, p)) ctx->perp[t.P].used = ++ctx->clock;
   hipStream_t s = (hipStream_t)hip_stream;
-  if (capturing(s)) pin_tables(ctx, N, r.flags);
+  if (capturing(s)) pin_tables(ctx, N, r.flags, p);
   // every grid on the caller's stream; the kernels write every workspace
   // value before reading it, so nothing needs clearing between calls
   return p == NMC_F64 ? run_group<double>(ctx, &r, 1, ctx->scratch, s, s)
@@ -2004,7 +2010,9 @@ int nmc_green_spectrum(nmc_ctx* ctx, int N, nmc_precision p, void* out, void* hi
   // the tables count against the budget like those of a solve
   // (every solve of this N finds its tables afterwards, nmc_solve_noalloc)
   TablePlan plan;
-  plan.read = tables_of(N, 0);
+  plan.read.push_back({P});
+  add_tables<double>(plan.read, N, 0, kMaxScaledP);
+  add_tables<float>(plan.read, N, 0, kMaxScaledP);
   plan.read[0].z64 = plan.read[0].z32 = true;
   plan.shared = cube_bytes(P, 24);
   if ((rc = prepare_tables(ctx, plan, s))) return rc;
@@ -2014,8 +2022,8 @@ int nmc_green_spectrum(nmc_ctx* ctx, int N, nmc_precision p, void* out, void* hi
   for (int n : {N / 2, N / 4})
     if (n >= kMinN && n % 4 == 0 && n <= 64) {
       const unsigned method = n == N / 2 ? NMC_MODIFIED : NMC_MODIFIED3;
-      add_tables<double>(scaled, n, method);
-      add_tables<float>(scaled, n, method);
+      add_tables<double>(scaled, n, method, kMaxScaledP);
+      add_tables<float>(scaled, n, method, kMaxScaledP);
     }
   if ((rc = build_spare(ctx, scaled, s))) return rc;
   const size_t H = P / 2 + 1, n = H * H * H;
