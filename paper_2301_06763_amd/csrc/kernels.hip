@@ -1699,10 +1699,6 @@ __global__ void __launch_bounds__(256) k_carry_tri(CarryTable tab, int N, int n)
 // second-order one-sided difference; covered cells use the level's own
 // values.
 template <class R>
-struct AccelScale {
-  R inv2h[16];  // 1 / (2 h_l) per level
-};
-template <class R>
 __device__ __forceinline__ R accel_neighbour(const R* __restrict__ P, const R* __restrict__ Pc,
                                              const R* __restrict__ Pf, int N, int z, int y, int x,
                                              bool centre_in) {
@@ -1789,7 +1785,7 @@ __device__ __forceinline__ R accel_foreign(const R* __restrict__ Pc, const R* __
 // against one cell a thread with every rule asked for each of its neighbours.
 template <class R, int V, int ZB>
 __global__ void __launch_bounds__(256) k_accel_rows(const R* __restrict__ phi, R* __restrict__ g, int N, int L,
-                                                    AccelScale<R> sc) {
+                                                    double h0) {
   struct alignas(V * sizeof(R)) Vec {
     R v[V];
   };
@@ -1806,7 +1802,7 @@ __global__ void __launch_bounds__(256) k_accel_rows(const R* __restrict__ phi, R
   const R* const Pc = P - n3;  // levels above 0 only
   const R* const Pf = l + 1 < L ? P + n3 : nullptr;
   const int lo = N / 4, hi = 3 * N / 4;
-  const R inv2h = sc.inv2h[l];
+  const R inv2h = (R)1 / (2 * (R)ldexp(h0, -l));
   // rows z0 - 1 .. z0 + ZB of the thread's cells, and the neighbours along x
   // and y of the ZB in the middle: all loads first
   const R* const row0 = P + (size_t)z0 * plane + y * N;
@@ -1902,11 +1898,12 @@ __global__ void __launch_bounds__(256) k_accel_rows(const R* __restrict__ phi, R
   }
 }
 
-// The same, one cell per thread: small levels (a thread's cells could meet
-// two such neighbours along x) and arrays not 16-byte aligned.
+// The same, one cell per thread: small levels (a thread's cells could meet two
+// such neighbours along x, or too few threads are left) and arrays not 16-byte
+// aligned.
 template <class R>
 __global__ void __launch_bounds__(256) k_accel(const R* __restrict__ phi, R* __restrict__ g, int N, int L,
-                                               AccelScale<R> sc) {
+                                               double h0) {
   const size_t n3 = (size_t)N * N * N;
   const int l = blockIdx.z, z = blockIdx.y;
   const int col = blockIdx.x * 256 + threadIdx.x;  // 32-bit: no 64-bit division
@@ -1915,7 +1912,7 @@ __global__ void __launch_bounds__(256) k_accel(const R* __restrict__ phi, R* __r
   const R* P = phi + (size_t)l * n3;
   const R* Pc = l > 0 ? P - n3 : nullptr;
   const R* Pf = l + 1 < L ? P + n3 : nullptr;
-  const R inv2h = sc.inv2h[l];
+  const R inv2h = (R)1 / (2 * (R)ldexp(h0, -l));
 #pragma unroll
   for (int comp = 0; comp < 3; ++comp)
     g[((size_t)l * 3 + comp) * n3 + (size_t)z * N * N + col] = accel_at(P, Pc, Pf, N, l, z, y, x, comp, inv2h);
@@ -2309,19 +2306,19 @@ hipError_t launch_inv_yx(const FieldTable& ft, PassGeom g, Tables<R> tb, hipStre
 
 template <class R>
 hipError_t launch_accel(const R* phi, R* g, int N, int L, double h0, hipStream_t s) {
-  AccelScale<R> sc{};
-  for (int l = 0; l < L; ++l) {
-    const R h = (R)std::ldexp(h0, -l);
-    sc.inv2h[l] = (R)1 / (2 * h);
-  }
-  // N is a multiple of 4, so rows keep the arrays' alignment
+  // Vector rows where the arrays are aligned (N is a multiple of 4, so rows keep
+  // that) and there are cells enough to fill the chip with V of them a thread:
+  // kernel time, one cell a thread / rows, FP64 20^3 x 2 4.3 / 4.4 us, 20^3 x 6
+  // 4.6 / 4.5, 32^3 x 6 5.9 / 4.8; FP32 32^3 x 2 4.2 / 4.8, 40^3 x 2 4.7 / 4.9,
+  // 28^3 x 6 5.3 / 5.1, 48^3 x 2 5.3 / 4.9.
   constexpr int V = 16 / (int)sizeof(R);
-  const bool rows = N >= 20 && (((uintptr_t)phi | (uintptr_t)g) & 15) == 0;
+  const bool rows = N >= 20 && (long long)L * N * N * N >= (sizeof(R) == 8 ? 25000 : 130000) &&
+                    (((uintptr_t)phi | (uintptr_t)g) & 15) == 0;
   const int zb = N >= 96 ? 2 : 1;  // k_accel_rows
   const dim3 grid((unsigned)((N * N / (rows ? V : 1) + 255) / 256), rows ? N / zb : N, L);
-  if (rows && zb == 2) launch(k_accel_rows<R, V, 2>, grid, dim3(256), 0, s, phi, g, N, L, sc);
-  else if (rows) launch(k_accel_rows<R, V, 1>, grid, dim3(256), 0, s, phi, g, N, L, sc);
-  else launch(k_accel<R>, grid, dim3(256), 0, s, phi, g, N, L, sc);
+  if (rows && zb == 2) launch(k_accel_rows<R, V, 2>, grid, dim3(256), 0, s, phi, g, N, L, h0);
+  else if (rows) launch(k_accel_rows<R, V, 1>, grid, dim3(256), 0, s, phi, g, N, L, h0);
+  else launch(k_accel<R>, grid, dim3(256), 0, s, phi, g, N, L, h0);
   return hipGetLastError();
 }
 

@@ -26,3 +26,13 @@ def test_rows_equal_cells(dtype, N, L):
         assert torch.equal(a, b)
     finally:
         ctx.close()
+
+
+# where the rule takes vector rows at the smallest N of each type, and sizes on
+# both sides of its line (L N^3 from 25 000 in FP64, 130 000 in FP32)
+@pytest.mark.timeout(120)
+@pytest.mark.parametrize("dtype,N,L", [(torch.float64, 20, 3), (torch.float64, 20, 4), (torch.float64, 28, 2),
+                                       (torch.float32, 24, 10), (torch.float32, 28, 6), (torch.float32, 40, 2),
+                                       (torch.float32, 44, 2), (torch.float32, 52, 1)])
+def test_rows_from_enough_cells(dtype, N, L):
+    test_rows_equal_cells(dtype, N, L)
