@@ -94,6 +94,13 @@ inline long long pyramid_slab(int N, int L) {
   return s;
 }
 inline bool pyramid_exact(int N, int L) { return L >= 2 && L - 1 <= 5 && N % (1 << L) == 0; }
+// The cascade of all levels in one launch up to kCascadeOneN cells, in two up to
+// kCascadeN, where one per level would be more: small levels are latency, and
+// from eight launches on the host's wait for a single call costs 12 us and more
+// in the runtime.  Us a solve, a launch per level / two / one: FP64 16^3 x 6
+// 44.2 / 32.7 / 31.3, 20^3 x 6 46.1 / 41.5 / 43.9, 32^3 x 6 50.6 / 46.7; 36^3 x 4
+// 55.1 / 56.4, 60^3 x 4 63.7 / 75.9; waited for alone, 32^3 x 6 112 / 62.
+constexpr int kCascadeOneN = 16, kCascadeN = 32;
 constexpr int kMaxPyramidDepth = 5;  // blocks up to 32^3 cells per workgroup
 // Edge of the cube of level k a workgroup reduces: a multiple of 2^k that
 // divides N, grown up to 16 cells when N allows.
@@ -270,6 +277,10 @@ template <class R> hipError_t launch_plane_spectrum(int P, int C, const double* 
 // launch (any N); fine_rc is the finished restriction of level l+1 or null.
 template <class R>
 hipError_t launch_restrict(const R* fine, const R* fine_rc, R* rc_out, int N, hipStream_t);
+// The same for every level of up to kMaxPyramidsPerLaunch requests in one or two
+// launches (N <= kCascadeN): level l's values at pyr + l * slab (PyramidDesc).
+template <class R>
+hipError_t launch_restrict_cascade(const PyramidTable&, int count, int N, int maxL, hipStream_t);
 // Block-mean pyramids of every level k >= 1 of up to kMaxPyramidsPerLaunch
 // requests in one launch (requires pyramid_exact(N, L) for each).
 template <class R>

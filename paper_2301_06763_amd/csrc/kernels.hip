@@ -1464,14 +1464,12 @@ __global__ void __launch_bounds__((PlaneCfg<R, P>::NTH)) k_inv_yx(FieldTable ft,
 }
 
 // ---------------------------------------------------------------------------
-// Restriction: mean of the 2^3 children of every child-region cell.
+// Restriction: mean of the 2^3 children of child-region cell (az, ay, ax); a
+// child inside the finer level's own child region takes its restriction fine_rc
+// (when set).
 template <class R>
-__global__ void k_restrict(const R* __restrict__ fine, const R* __restrict__ fine_rc,
-                           R* __restrict__ rc, int N) {
+__device__ __forceinline__ R restrict_cell(const R* fine, const R* fine_rc, int N, int az, int ay, int ax) {
   const int N2 = N / 2, lo = N / 4, hi = 3 * N / 4;
-  const int id = blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= N2 * N2 * N2) return;
-  const int ax = id % N2, ay = (id / N2) % N2, az = id / (N2 * N2);
   R s = 0;
 #pragma unroll
   for (int bz = 0; bz < 2; ++bz)
@@ -1484,7 +1482,49 @@ __global__ void k_restrict(const R* __restrict__ fine, const R* __restrict__ fin
         s += cen ? fine_rc[((size_t)(z - lo) * N2 + (y - lo)) * N2 + (x - lo)]
                  : fine[((size_t)z * N + y) * N + x];
       }
-  rc[id] = s * (R)0.125;
+  return s * (R)0.125;
+}
+template <class R>
+__global__ void k_restrict(const R* __restrict__ fine, const R* __restrict__ fine_rc,
+                           R* __restrict__ rc, int N) {
+  const int N2 = N / 2, id = blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= N2 * N2 * N2) return;
+  rc[id] = restrict_cell(fine, fine_rc, N, id / (N2 * N2), id / N2 % N2, id % N2);
+}
+// The cells of every level that wait for no other level: all of the finest
+// restriction's, elsewhere those without a child in the child region.
+__device__ __forceinline__ bool restrict_waits(int N, int az, int ay, int ax) {
+  const int lo = N / 4, hi = 3 * N / 4;
+  auto meets = [&](int a) { return 2 * a + 1 >= lo && 2 * a < hi; };
+  return meets(az) && meets(ay) && meets(ax);
+}
+template <class R>
+__global__ void __launch_bounds__(256) k_restrict_outer(PyramidTable tab, int N) {
+  const PyramidDesc& D = tab.r[blockIdx.z];
+  const int l = blockIdx.y, N2 = N / 2, id = blockIdx.x * 256 + threadIdx.x;
+  if (l > D.L - 2 || id >= N2 * N2 * N2) return;
+  const int az = id / (N2 * N2), ay = id / N2 % N2, ax = id % N2;
+  if (l < D.L - 2 && restrict_waits(N, az, ay, ax)) return;
+  const R* const fine = static_cast<const R*>(D.rho) + (size_t)(l + 1) * N * N * N;
+  static_cast<R*>(D.pyr)[l * D.slab + id] = restrict_cell<R>(fine, nullptr, N, az, ay, ax);
+}
+// The others (INNER), an eighth of a level's, or all cells, level after level
+// from the finest in one workgroup per request.
+constexpr int kCascadeThreads = 1024;
+template <class R, bool INNER>
+__global__ void __launch_bounds__(kCascadeThreads) k_restrict_cascade(PyramidTable tab, int N) {
+  const PyramidDesc& D = tab.r[blockIdx.x];
+  const int N2 = N / 2, c0 = INNER ? N / 4 / 2 : 0, m = INNER ? (3 * N / 4 + 1) / 2 - c0 : N2;
+  for (int l = D.L - (INNER ? 3 : 2); l >= 0; --l) {
+    const R* const fine = static_cast<const R*>(D.rho) + (size_t)(l + 1) * N * N * N;
+    R* const rc = static_cast<R*>(D.pyr) + l * D.slab;
+    const R* const fine_rc = l < D.L - 2 ? rc + D.slab : nullptr;
+    for (int i = threadIdx.x; i < m * m * m; i += kCascadeThreads) {
+      const int az = c0 + i / (m * m), ay = c0 + i / m % m, ax = c0 + i % m;
+      rc[(az * N2 + ay) * N2 + ax] = restrict_cell(fine, fine_rc, N, az, ay, ax);
+    }
+    __syncthreads();  // rc is the next level's fine_rc
+  }
 }
 
 // Block-mean pyramids (the unrolled restriction, kernels.h).  A workgroup
@@ -2328,6 +2368,16 @@ hipError_t launch_restrict(const R* fine, const R* fine_rc, R* rc, int N, hipStr
   launch(k_restrict<R>, dim3((n + 255) / 256), dim3(256), 0, s, fine, fine_rc, rc, N);
   return hipGetLastError();
 }
+template <class R>
+hipError_t launch_restrict_cascade(const PyramidTable& tab, int count, int N, int maxL, hipStream_t s) {
+  if (N <= kCascadeOneN) {
+    launch(k_restrict_cascade<R, false>, dim3(count), dim3(kCascadeThreads), 0, s, tab, N);
+  } else {
+    launch(k_restrict_outer<R>, dim3((N * N * N / 8 + 255) / 256, maxL - 1, count), dim3(256), 0, s, tab, N);
+    if (maxL > 2) launch(k_restrict_cascade<R, true>, dim3(count), dim3(kCascadeThreads), 0, s, tab, N);
+  }
+  return hipGetLastError();
+}
 
 template <class R>
 hipError_t launch_pyramid(const PyramidTable& tab, int count, int N, int maxL, hipStream_t s) {
@@ -2432,6 +2482,7 @@ hipError_t launch_fft_lines(const void* in, void* out, int P, int nlines, int di
   template hipError_t launch_inv_yx<R>(const FieldTable&, PassGeom, Tables<R>, hipStream_t);      \
   template bool plane_passes_fit<R>(int);                                                         \
   template hipError_t launch_restrict<R>(const R*, const R*, R*, int, hipStream_t);               \
+  template hipError_t launch_restrict_cascade<R>(const PyramidTable&, int, int, int, hipStream_t);  \
   template hipError_t launch_pyramid<R>(const PyramidTable&, int, int, int, hipStream_t);          \
   template hipError_t launch_carry<R>(const CarryTable&, int, int, int, hipStream_t);              \
   template hipError_t launch_carry_tri<R>(const CarryTable&, int, int, int, hipStream_t);          \

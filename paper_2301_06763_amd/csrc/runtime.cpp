@@ -742,13 +742,18 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
     const R* fine_rc;
     R* out;
   };
-  std::vector<RestrictStep> restricts;  // cascaded restriction (N not a multiple of 2^L)
-  std::vector<nmc::PyramidDesc> pyramids;
-  int pyr_maxL = 0;
+  std::vector<RestrictStep> restricts;  // cascaded restriction (N not a multiple of 2^L), a launch per level
+  std::vector<nmc::PyramidDesc> pyramids, cascades;
+  int pyr_maxL = 0, cas_maxL = 0;
   std::vector<nmc::CarryDesc> carries;  // hole pipeline: S_n, n = 1 .. L-2
   std::vector<int> carry_levels;
   int maxL = 0;
   size_t off = 0;
+  // cascaded restriction: of all levels together where that is fewer launches
+  int steps = 0;
+  for (int i = 0; i < count; ++i)
+    if (!(reqs[i].flags & NMC_NO_RESTRICT) && !nmc::pyramid_exact(N, reqs[i].L)) steps += reqs[i].L - 1;
+  const bool together = N <= nmc::kCascadeOneN ? steps > 1 : N <= nmc::kCascadeN && steps > 2;
   for (int i = 0; i < count; ++i) {
     const Req& q = reqs[i];
     const Layout lo = make_layout(N, q.L, q.p, q.flags);
@@ -765,6 +770,9 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
       if (pyramid) {
         pyramids.push_back({rho, base + lo.Rc(0), rslab, q.L});
         pyr_maxL = std::max(pyr_maxL, q.L);
+      } else if (together) {
+        cascades.push_back({rho, base + lo.Rc(0), rslab, q.L});
+        cas_maxL = std::max(cas_maxL, q.L);
       } else {
         for (int l = q.L - 2; l >= 0; --l) {
           const R* fine_rc = (l + 1 <= q.L - 2) ? (const R*)(base + lo.Rc(l + 1)) : nullptr;
@@ -961,6 +969,17 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
       }
       ProfScope ps(ctx, st, NMC_PASS_RESTRICT, bytes);
       NMC_HIP(ctx, nmc::launch_pyramid<R>(tab, cnt, N, pyr_maxL, st));
+    }
+    for (size_t a = 0; a < cascades.size(); a += nmc::kMaxPyramidsPerLaunch) {
+      nmc::PyramidTable tab{};
+      const int cnt = (int)std::min<size_t>(nmc::kMaxPyramidsPerLaunch, cascades.size() - a);
+      double bytes = 0;
+      for (int k = 0; k < cnt; ++k) {
+        tab.r[k] = cascades[a + k];
+        bytes += (double)(tab.r[k].L - 1) * (nn + nn / 8) * sizeof(R);
+      }
+      ProfScope ps(ctx, st, NMC_PASS_RESTRICT, bytes);
+      NMC_HIP(ctx, nmc::launch_restrict_cascade<R>(tab, cnt, N, cas_maxL, st));
     }
     for (const auto& r : restricts) {
       ProfScope ps(ctx, st, NMC_PASS_RESTRICT, (nn + nn / 8) * sizeof(R));

@@ -231,6 +231,8 @@ hipError_t launch_restrict(const R*, const R*, R* out, int, hipStream_t s) { ret
 template <class R>
 hipError_t launch_pyramid(const PyramidTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].pyr}); }
 template <class R>
+hipError_t launch_restrict_cascade(const PyramidTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].pyr}); }
+template <class R>
 hipError_t launch_carry(const CarryTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].S}); }
 template <class R>
 hipError_t launch_carry_tri(const CarryTable& t, int, int, int, hipStream_t s) { return op_on(s, {t.r[0].S}); }

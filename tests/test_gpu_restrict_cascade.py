@@ -1,0 +1,37 @@
+"""Restriction of levels whose N is no multiple of 2^L, all levels in one launch (up
+to 16 cells) or two (up to 32): the smallest N, children of both kinds under one
+cell (N/4 odd), the deepest nests, and batches whose requests differ in L.  One
+request's solve with a launch per level (two levels, or N above 32) and the oracle
+are the references."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2301_06763_amd import inputs, nmc
+
+pytestmark = pytest.mark.gpu
+
+TOL = {torch.float64: 1e-12, torch.float32: 1e-5}  # the pointwise bounds of every parity test
+
+
+@pytest.mark.timeout(120)
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("N,L", [(4, 3), (4, 16), (8, 4), (12, 5), (16, 6), (20, 4), (20, 9), (24, 5), (28, 4), (32, 7)])
+def test_cascade_matches_oracle(dtype, N, L):
+    w = inputs.random_levels(N, L, seed=520 + N + L)
+    rho = w.rho.to("cuda", dtype)
+    ctx = nmc.Context()
+    try:
+        got = ctx.solve(rho, w.h0)
+        ref = oracle.solve(rho.double().cpu().numpy(), w.h0)
+        assert np.max(np.abs(got.double().cpu().numpy() - ref) / np.abs(ref)) < TOL[dtype]
+        # with shallower nests in one call: each as alone
+        items = [(inputs.random_levels(N, l, seed=530 + l).rho.to("cuda", dtype), w.h0) for l in (2, 3, L, 1)]
+        alone = [ctx.solve(r, h).clone() for r, h in items]
+        both = ctx.solve_batch(items)
+        torch.cuda.synchronize()
+        for a, b in zip(alone, both):
+            assert torch.equal(a, b)
+    finally:
+        ctx.close()
