@@ -94,13 +94,15 @@ inline long long pyramid_slab(int N, int L) {
   return s;
 }
 inline bool pyramid_exact(int N, int L) { return L >= 2 && L - 1 <= 5 && N % (1 << L) == 0; }
-// The cascade of all levels in one launch up to kCascadeOneN cells, in two up to
-// kCascadeN, where one per level would be more: small levels are latency, and
+// The cascade of all levels in one launch up to kCascadeOneN cells, in two where
+// cascade_in_two, if one per level would be more: small levels are latency, and
 // from eight launches on the host's wait for a single call costs 12 us and more
-// in the runtime.  Us a solve, a launch per level / two / one: FP64 16^3 x 6
-// 44.2 / 32.7 / 31.3, 20^3 x 6 46.1 / 41.5 / 43.9, 32^3 x 6 50.6 / 46.7; 36^3 x 4
-// 55.1 / 56.4, 60^3 x 4 63.7 / 75.9; waited for alone, 32^3 x 6 112 / 62.
-constexpr int kCascadeOneN = 16, kCascadeN = 32;
+// in the runtime.  Us a solve, a launch per level / two / one: FP64 16^3 x 8
+// 53.2 / 40.5 / 36.7, 20^3 x 6 46.6 / 42.2 / 44.9, 32^3 x 6 50.6 / 46.7, 40^3 x 6
+// 71.0 / 69.3, 44^3 x 6 73.7 / 80.0; waited for alone, 32^3 x 6 112 / 62, 40^3 x 6
+// 113 / 85.  More cells wait for a finer level where N/4 is odd (36^3 x 6 68.2 / 69.3).
+constexpr int kCascadeOneN = 16;
+constexpr bool cascade_in_two(int N) { return N <= (N % 8 ? 32 : 40); }
 constexpr int kMaxPyramidDepth = 5;  // blocks up to 32^3 cells per workgroup
 // Edge of the cube of level k a workgroup reduces: a multiple of 2^k that
 // divides N, grown up to 16 cells when N allows.
@@ -278,7 +280,7 @@ template <class R> hipError_t launch_plane_spectrum(int P, int C, const double* 
 template <class R>
 hipError_t launch_restrict(const R* fine, const R* fine_rc, R* rc_out, int N, hipStream_t);
 // The same for every level of up to kMaxPyramidsPerLaunch requests in one or two
-// launches (N <= kCascadeN): level l's values at pyr + l * slab (PyramidDesc).
+// launches: level l's values at pyr + l * slab (PyramidDesc).
 template <class R>
 hipError_t launch_restrict_cascade(const PyramidTable&, int count, int N, int maxL, hipStream_t);
 // Block-mean pyramids of every level k >= 1 of up to kMaxPyramidsPerLaunch

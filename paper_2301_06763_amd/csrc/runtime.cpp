@@ -753,7 +753,7 @@ int run_group(nmc_ctx* ctx, const Req* reqs, int count, char* ws, hipStream_t s,
   int steps = 0;
   for (int i = 0; i < count; ++i)
     if (!(reqs[i].flags & NMC_NO_RESTRICT) && !nmc::pyramid_exact(N, reqs[i].L)) steps += reqs[i].L - 1;
-  const bool together = N <= nmc::kCascadeOneN ? steps > 1 : N <= nmc::kCascadeN && steps > 2;
+  const bool together = N <= nmc::kCascadeOneN ? steps > 1 : nmc::cascade_in_two(N) && steps > 2;
   for (int i = 0; i < count; ++i) {
     const Req& q = reqs[i];
     const Layout lo = make_layout(N, q.L, q.p, q.flags);

@@ -1,7 +1,7 @@
 """Restriction of levels whose N is no multiple of 2^L, all levels in one launch (up
-to 16 cells) or two (up to 32): the smallest N, children of both kinds under one
+to 16 cells) or two (up to 40): the smallest N, children of both kinds under one
 cell (N/4 odd), the deepest nests, and batches whose requests differ in L.  One
-request's solve with a launch per level (two levels, or N above 32) and the oracle
+request's solve with a launch per level (two levels, or N above 40) and the oracle
 are the references."""
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ TOL = {torch.float64: 1e-12, torch.float32: 1e-5}  # the pointwise bounds of eve
 
 @pytest.mark.timeout(120)
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("N,L", [(4, 3), (4, 16), (8, 4), (12, 5), (16, 6), (20, 4), (20, 9), (24, 5), (28, 4), (32, 7)])
+@pytest.mark.parametrize("N,L", [(4, 3), (4, 16), (8, 4), (12, 5), (16, 6), (20, 4), (20, 9), (24, 5), (28, 4), (32, 7), (36, 5), (40, 6)])
 def test_cascade_matches_oracle(dtype, N, L):
     w = inputs.random_levels(N, L, seed=520 + N + L)
     rho = w.rho.to("cuda", dtype)
