@@ -152,8 +152,8 @@ int nmc_footprint_bytes_flags(int N, int L, nmc_precision p, unsigned flags, siz
  * While hip_stream is being captured into a graph, the call takes workspace of
  * its own and holds it, like the Green tables it reads, until nmc_destroy (the
  * graph may be launched at any time; launches of one graph must follow one
- * another).  The tables must be resident (NMC_EDEVICE otherwise: solve this N
- * and method once before), and workspace that no cached block serves needs a
+ * another).  The tables must be resident (NMC_EDEVICE otherwise: solve this N,
+ * method and precision once before), and workspace that no cached block serves needs a
  * capture mode that allows hipMalloc; nmc_solve_noalloc allocates nothing.
  * The same holds for nmc_solve_batch.
  * Errors: NMC_EINVAL, NMC_EUNSUPPORTED, NMC_ENOMEM, NMC_EDEVICE. */

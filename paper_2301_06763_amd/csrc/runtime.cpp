@@ -52,8 +52,11 @@ size_t real_size(nmc_precision p) { return p == NMC_F64 ? 8 : 4; }
 //  * child-region boxes (kind 1): the child region alone in an (N/2+2)^3 box,
 //    Phi_hole = Phi - C, and S_l = Phi(Omega^l) - C_l left by the last pass of
 //    level l.  Cheaper grids but, in the separate passes, one last-pass launch
-//    per level, which pays from N = 128 up (measured).  Levels convolved plane
-//    by plane always take boxes: their last passes leave Phi - C for the cascade.
+//    per level, which pays from N = 128 up (measured with boxes on the level's
+//    period; on half of it, an eighth of the points, not measured again: the
+//    sizes in question are FP64 100 to 124).  Levels convolved plane by plane
+//    take boxes too, whose last pass leaves Phi - C for the cascade, but hole
+//    grids below 128 cells where the caller keeps its coarse density (run_group).
 bool use_boxes(int N) { return N >= 128; }
 
 // The modified method (Sect. 7, Appendix B) convolves a doubled grid per
