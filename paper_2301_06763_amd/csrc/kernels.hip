@@ -1739,6 +1739,10 @@ __global__ void __launch_bounds__(256) k_carry_tri(CarryTable tab, int N, int n)
 // second-order one-sided difference; covered cells use the level's own
 // values.
 template <class R>
+struct AccelScale {
+  R inv2h[16];  // 1 / (2 h_l) per level
+};
+template <class R>
 __device__ __forceinline__ R accel_neighbour(const R* __restrict__ P, const R* __restrict__ Pc,
                                              const R* __restrict__ Pf, int N, int z, int y, int x,
                                              bool centre_in) {
@@ -1825,7 +1829,7 @@ __device__ __forceinline__ R accel_foreign(const R* __restrict__ Pc, const R* __
 // against one cell a thread with every rule asked for each of its neighbours.
 template <class R, int V, int ZB>
 __global__ void __launch_bounds__(256) k_accel_rows(const R* __restrict__ phi, R* __restrict__ g, int N, int L,
-                                                    double h0) {
+                                                    AccelScale<R> sc) {
   struct alignas(V * sizeof(R)) Vec {
     R v[V];
   };
@@ -1842,7 +1846,7 @@ __global__ void __launch_bounds__(256) k_accel_rows(const R* __restrict__ phi, R
   const R* const Pc = P - n3;  // levels above 0 only
   const R* const Pf = l + 1 < L ? P + n3 : nullptr;
   const int lo = N / 4, hi = 3 * N / 4;
-  const R inv2h = (R)1 / (2 * (R)ldexp(h0, -l));
+  const R inv2h = sc.inv2h[l];
   // rows z0 - 1 .. z0 + ZB of the thread's cells, and the neighbours along x
   // and y of the ZB in the middle: all loads first
   const R* const row0 = P + (size_t)z0 * plane + y * N;
@@ -2355,9 +2359,11 @@ hipError_t launch_accel(const R* phi, R* g, int N, int L, double h0, hipStream_t
   const bool rows = N >= 20 && (long long)L * N * N * N >= (sizeof(R) == 8 ? 25000 : 130000) &&
                     (((uintptr_t)phi | (uintptr_t)g) & 15) == 0;
   const int zb = N >= 96 ? 2 : 1;  // k_accel_rows
+  AccelScale<R> sc{};
+  for (int l = 0; rows && l < L; ++l) sc.inv2h[l] = (R)1 / (2 * (R)std::ldexp(h0, -l));
   const dim3 grid((unsigned)((N * N / (rows ? V : 1) + 255) / 256), rows ? N / zb : N, L);
-  if (rows && zb == 2) launch(k_accel_rows<R, V, 2>, grid, dim3(256), 0, s, phi, g, N, L, h0);
-  else if (rows) launch(k_accel_rows<R, V, 1>, grid, dim3(256), 0, s, phi, g, N, L, h0);
+  if (rows && zb == 2) launch(k_accel_rows<R, V, 2>, grid, dim3(256), 0, s, phi, g, N, L, sc);
+  else if (rows) launch(k_accel_rows<R, V, 1>, grid, dim3(256), 0, s, phi, g, N, L, sc);
   else launch(k_accel<R>, grid, dim3(256), 0, s, phi, g, N, L, h0);
   return hipGetLastError();
 }
